@@ -132,14 +132,56 @@ struct PoolBits {
   }
 };
 
-// Wave-uniform scalars of one instance.
+// Wave-uniform scalars of one instance.  At most 1,024 jobs of fewer than 2^20
+// tokens run at once and their starts lie within 2^20 steps of each other, so
+// the reservations, and every sum over the active jobs of (start - earliest
+// start), of footprints or of footprint differences, stay below 2^31: they are
+// held in 32 bits.  sum_s itself (and sp - sum_s) is kept modulo 2^32, and only
+// differences of that kind are read from it.
 struct SimState {
   int t, ndone, nact, min_s, max_s, min_end;
-  int64_t res, sum_s, sum_comp;
+  int res;              // KV reservations of the active jobs
+  uint32_t sum_s;       // summed start of the active jobs, modulo 2^32
+  uint64_t sum_start;   // summed start of every admitted job
   // prefill variant: largest prompt - start and summed prompt of the active jobs
   // (the largest footprint at step t is t + G + 1)
   int G;
-  int64_t sp;
+  uint32_t sp;
+};
+
+// acc += a * b, one 32 x 32 -> 64-bit multiply-add.
+__device__ __forceinline__ void mac(uint64_t& acc, uint32_t a, uint32_t b) {
+  acc += (uint64_t)a * b;
+}
+
+// Section 5 sums of the event-free spans.  Over a span of D steps with s active
+// jobs, first largest footprint m0, externality xe per step and extent ext:
+//   E += D xe; the largest footprints m0, m0 + 1, .. sum to D m0 + D (D - 1) / 2,
+// kept doubled (SM2, and SSM2 times s) so that each is one product of 32-bit
+// factors: s D < 2^30 and 2 m0 + D < 2^23.  The tokens held are largest at the
+// span's last step: s (m0 + D - 1) - xe.
+// The event loop is bound by instruction issue on both the vector and the
+// scalar unit, and these sums are its largest scalar part: with 64-bit factors
+// they took about 120 scalar instructions per event, now about 40 (65,536 x 2,000
+// ISJL at B = 512: 6.23 -> 5.72 ms; 16,384 x 2,000 FCFS, where every completion
+// is an event: 13.3 -> 10.9 ms).
+struct SpanSums {
+  uint64_t E, SM2, SSM2, X;
+  uint32_t unfair, peak;
+  __device__ __forceinline__ void clear() {
+    E = SM2 = SSM2 = X = 0;
+    unfair = peak = 0;
+  }
+  __device__ __forceinline__ void add(uint32_t D, uint32_t s, uint32_t m0, uint32_t xe, int ext,
+                                      int alpha) {
+    const uint32_t m2 = 2u * m0 + D - 1u;
+    mac(E, D, xe);
+    mac(SM2, D, m2);
+    mac(SSM2, s * D, m2);
+    mac(X, D, (uint32_t)ext);
+    unfair += ext > alpha ? D : 0u;
+    peak = max(peak, s * (m0 + D - 1u) - xe);
+  }
 };
 
 // ROB: Robust-ISJL (Section 3.4): ordering, packs, caps and the KV reservation
@@ -218,6 +260,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   const int NP = a.NP;
   int bad = 0, big = 0, unsorted = 0, maxlen = 0, maxfoot = 0, maxarr = 0;
   int64_t osum = 0, qsum = 0, rsum = 0;
+  int64_t lsum = 0;  // PRE: summed service length (else osum)
   uint64_t q2 = 0;  // twice the footprint sum Q: one 32 x 32 -> 64 product per job
   int carry_ar = 0;
   // The rows are software-pipelined: the loads of row r + PF are issued
@@ -273,6 +316,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       q2 += PRE ? (uint64_t)(uint32_t)o * (uint32_t)(2 * p + o + 1)
                 : (uint64_t)(uint32_t)len * (uint32_t)(len + 1);
       rsum += ar;
+      if (PRE) lsum += o;
       const uint32_t l32 = (uint32_t)(ROB ? plan_len : len) & LMASK;
       if (POL == POL_LJF || POL == POL_ISJL) key = ((LMASK - l32) << 12) | (uint32_t)i;
       else if (POL == POL_SJF) key = (l32 << 12) | (uint32_t)i;
@@ -303,6 +347,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   osum = wave_sum64(osum);
   qsum = (int64_t)((uint64_t)wave_sum64((int64_t)q2) >> 1);  // every term is even
   rsum = wave_sum64(rsum);
+  lsum = PRE ? wave_sum64(lsum) : osum;
   if (GEN && maxarr >= ARR_LIMIT) {
     write_marker(a.out, a.out_T, inst, FSCHED_T_TOOLARGE, lane);
     return;
@@ -358,7 +403,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   // ---- state ---------------------------------------------------------------
   const int Beff = a.Beff;
   const int alpha = a.alpha;
-  const int64_t M = a.M;
+  // reservations stay below 2^30, so a larger budget never binds
+  const int M = a.M < (int64_t)IDLE ? (int)a.M : IDLE;
   int ws_start[K], ws_end[K];
   int ws_plan[K];  // ROB: KV reservation of the running job (from its planning size)
   int ws_p[K];     // PRE: prompt of the running job (its footprint offset)
@@ -409,23 +455,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   S.min_end = IDLE;
   S.res = 0;
   S.sum_s = 0;
-  S.sum_comp = 0;
+  S.sum_start = 0;
   S.G = -IDLE;
   S.sp = 0;
   // C = c T + tau sum_t |S_t| m_t and W = c T + tau sum_t m_t (m_t: the largest
   // footprint at step t, 0 when idle): c and tau are applied once at the end
   // (every step 0 .. T-1 is accounted exactly once)
-  int64_t acc_E = 0, acc_SM = 0, acc_SSM = 0, acc_ext = 0, acc_busy = 0, acc_peak = 0,
-          acc_unfair = 0;
-  int acc_maxext = 0, acc_maxact = 0;
+  SpanSums acc;
+  acc.clear();
+  int acc_busy = 0, acc_maxext = 0, acc_maxact = 0;  // every makespan is below 2^31
   // With up to 2 slots per lane the sweeps' per-lane partial sums (and the
   // largest footprint) of their span terms carry over from sweep to sweep and
   // are summed over the wave once after the event loop: integer sums, so the
   // deferral changes no result, and a sweep ends without a reduction.  The
   // wider kernels have no registers to spare for them and reduce per sweep.
   constexpr bool DEFER = K <= 2;
-  int64_t pE = 0, pSM = 0, pSSM = 0, pX = 0, pP = 0;
-  int pU = 0;
+  SpanSums lane_sums;
+  lane_sums.clear();
+  auto reduce_lane_sums = [&](const SpanSums& l) {
+    acc.E += (uint64_t)wave_sum64((int64_t)l.E);
+    acc.SM2 += (uint64_t)wave_sum64((int64_t)l.SM2);
+    acc.SSM2 += (uint64_t)wave_sum64((int64_t)l.SSM2);
+    acc.X += (uint64_t)wave_sum64((int64_t)l.X);
+    acc.unfair += (uint32_t)wave_sum((int)l.unfair);
+    acc.peak = max(acc.peak, (uint32_t)wave_max((int)l.peak));  // below 2^31
+  };
   int32_t* st_out = a.start ? a.start + row : nullptr;
   int32_t* fi_out = a.finish ? a.finish + row : nullptr;
   const int iter_max = 8 * n + 64;
@@ -532,12 +586,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   // (strict order; a job that would run alone always fits), onto the first
   // eligible idle workers in index order (ISJL Phase TWO also needs an empty
   // plan queue).  Returns the number admitted.
-  auto admit_prefix = [&](int t, int G, bool need_empty_queue, int& adm, int64_t& adm_len,
+  auto admit_prefix = [&](int t, int G, bool need_empty_queue, int& adm,
                           int& adm_minlen) -> int {
     int na = G;
-    int64_t tot64 = -1;  // summed length of the admitted jobs, when the KV scan found it
+    int ptot = -1;  // summed reservation of the admitted jobs, when the KV scan found it
     if (M != 0) {
-      int64_t run = S.res;
+      int run = S.res;
       for (int c0 = 0; c0 < G; c0 += WAVE) {
         const int j = c0 + lane;
         int len = 0;
@@ -556,14 +610,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
         }
         run += readlane(pre, 63);
       }
-      tot64 = run - S.res;
+      ptot = run - S.res;
     }
     // the count in a scalar register, so the walk over the slot registers
     // below branches on it rather than masking lanes (measured on the kernels
     // with more than 2 slots per lane; the narrower ones ran no faster)
     if constexpr (K > 2) na = uni(na);
     if (na == 0) return 0;
-    int base = 0, lsum = 0, lplan = 0, lmin = IDLE, lp = 0, lpmax = -IDLE;
+    int base = 0, lplan = 0, lmin = IDLE, lp = 0, lpmax = -IDLE;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       if (base < na) {
@@ -578,12 +632,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
           ws_start[k] = t;
           ws_end[k] = t + len;
           emit(pid(wv), t, len);
-          lsum += len;
           if (ROB || PRE) {
             const int rv = resv_len(pid(wv), plan);
             ws_plan[k] = rv;
             lplan += rv;
             lmin = min(lmin, len);
+          } else {
+            lplan += len;
           }
           if (PRE) {
             const int pp = P[pid(wv)];
@@ -595,25 +650,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
         base += __builtin_popcountll(bm);
       }
     }
-    int tot, ptot;  // true lengths and reservations admitted
+    if (ptot < 0) ptot = wave_sum(lplan);
     if (ROB || PRE) {
-      tot = wave_sum(lsum);
-      ptot = tot64 >= 0 ? (int)tot64 : wave_sum(lplan);
       adm_minlen = min(adm_minlen, wave_min(lmin));
     } else {
-      tot = ptot = tot64 >= 0 ? (int)tot64 : wave_sum(lsum);
       // the gathered jobs are in priority order, so the shortest admitted one
       // is the last (longest first) or the first (SJF)
       adm_minlen = min(adm_minlen, plen(W[STG[POL == POL_SJF ? 0 : na - 1]]));
     }
     if (PRE) {
-      S.sp += wave_sum(lp);
+      S.sp += (uint32_t)wave_sum(lp);
       S.G = max(S.G, wave_max(lpmax) - t);  // na >= 1 jobs were admitted
     }
     pool.clear_upto(STG[na - 1], lane);  // the first na queued ranks
     qcount -= na;
     adm += na;
-    adm_len += tot;
     S.res += ptot;
     S.nact += na;
     return na;
@@ -624,18 +675,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   // alone and the rest only if all 8 fit: admitting those 8 and then the prefix
   // of the next G - 8 is the same strict prefix, and a budget that stops early
   // spares the gather of all G.
-  auto admit_first = [&](int t, int G, bool need_empty_queue, int& adm, int64_t& adm_len,
+  auto admit_first = [&](int t, int G, bool need_empty_queue, int& adm,
                          int& adm_minlen) -> int {
     constexpr int G0 = 8;
     if (K <= 4 && M != 0 && S.nact > 0 && G > G0) {
       gather_first(G0);
-      const int na = admit_prefix(t, G0, need_empty_queue, adm, adm_len, adm_minlen);
+      const int na = admit_prefix(t, G0, need_empty_queue, adm, adm_minlen);
       if (na < G0) return na;
       gather_first(G - G0);
-      return G0 + admit_prefix(t, G - G0, need_empty_queue, adm, adm_len, adm_minlen);
+      return G0 + admit_prefix(t, G - G0, need_empty_queue, adm, adm_minlen);
     }
     gather_first(G);
-    return admit_prefix(t, G, need_empty_queue, adm, adm_len, adm_minlen);
+    return admit_prefix(t, G, need_empty_queue, adm, adm_minlen);
   };
 
   // FAIR: launched when every wave of the grid is resident at once, so that the
@@ -694,7 +745,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
         S.max_s = wave_max(mx);
       }
       if (PRE) {
-        S.sp -= wave_sum(lp);
+        S.sp -= (uint32_t)wave_sum(lp);
         if (ballot(hG)) {
           int g = -IDLE;
 #pragma unroll
@@ -706,7 +757,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       S.ndone += nret;
       S.nact -= nret;
       S.res -= (ROB || PRE) ? wave_sum(lplan) : lret;
-      S.sum_s -= (int64_t)nret * t - (int64_t)lret;
+      S.sum_s -= (uint32_t)nret * (uint32_t)t - (uint32_t)lret;
     }
     if (S.ndone == n) break;
 
@@ -765,7 +816,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
     const int amax = S.nact > 0 ? t - S.min_s : 0;
     const int nact0 = S.nact;
     int adm = 0, adm_minlen = IDLE;
-    int64_t adm_len = 0;
     bool kv_block = false;
     int free_empty = 0;  // ISJL: idle workers with nothing planned, after this step's admissions
 
@@ -780,7 +830,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
         int len = plen(wv), id = pid(wv);
         const int pp = (PRE && lane < c) ? P[id] : 0;  // prompt (prefill variant)
         int pre = wave_scan_incl(len + pp);            // reservations
-        bool fit = (M == 0) | ((int64_t)(S.res + pre) <= M) |
+        bool fit = (M == 0) | (S.res + pre <= M) |
                    ((S.nact == 0) & (done == 0) & (lane == 0));
         uint64_t fm = ballot((lane < c) & !fit);
         int take = fm ? __builtin_ctzll(fm) : c;
@@ -811,12 +861,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
           adm_minlen = min(adm_minlen, wave_min(lane < take ? len : IDLE));
           adm += take;
           if (PRE) {
-            const int lp = wave_sum(lane < take ? pp : 0);
-            adm_len += tl - lp;
-            S.sp += lp;
+            S.sp += (uint32_t)wave_sum(lane < take ? pp : 0);
             S.G = max(S.G, wave_max(lane < take ? pp : -IDLE) - t);
-          } else {
-            adm_len += tl;
           }
           S.res += tl;
           S.nact += take;
@@ -831,7 +877,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
         if (freew > 0) {
           const int kp = qcount;
           const int G = min(freew, kp);
-          if (G > 0 && !head_blocked()) admit_first(t, G, false, adm, adm_len, adm_minlen);
+          if (G > 0 && !head_blocked()) admit_first(t, G, false, adm, adm_minlen);
         }
       }
     } else {  // ISJL
@@ -853,7 +899,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
           // Bp: largest prefix of the longest jobs that fits the KV budget
           int Bp = G;
           if (M != 0) {
-            int64_t run = 0;
+            int run = 0;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
               if (k * WAVE < G && Bp == G) {
@@ -1075,7 +1121,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
             // Sequential KV check in worker order; a blocked worker waits and
             // later workers are still tried.
             int nk = 0;
-            int64_t rres = S.res;
+            int rres = S.res;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
               uint64_t mk = ballot(cand[k]);
@@ -1092,10 +1138,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
               }
               cand[k] = cand[k] && ((keep >> lane) & 1ull);
             }
-            tot = (int)(rres - S.res);
+            tot = rres - S.res;
             ncand = nk;
           }
-          int mlen = IDLE, ltrue = 0, lp = 0, lpmax = -IDLE;
+          int mlen = IDLE, lp = 0, lpmax = -IDLE;
 #pragma unroll
           for (int k = 0; k < K; ++k) {
             if (cand[k]) {
@@ -1105,10 +1151,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
               const int len = true_len(pid(wv), plan);
               ws_start[k] = t;
               ws_end[k] = t + len;
-              if (ROB || PRE) {
-                ws_plan[k] = clen[k];
-                ltrue += len;
-              }
+              if (ROB || PRE) ws_plan[k] = clen[k];
               if (PRE) {
                 const int pp = P[pid(wv)];
                 ws_p[k] = pp;
@@ -1129,13 +1172,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
           }
           adm_minlen = min(adm_minlen, wave_min(mlen));
           adm += ncand;
-          adm_len += (ROB || PRE) ? wave_sum(ltrue) : tot;
           S.res += tot;
           if (PRE) {
             // the KV check may have dropped every candidate
             const int gm = wave_max(lpmax);
             if (gm != -IDLE) S.G = max(S.G, gm - t);
-            S.sp += wave_sum(lp);
+            S.sp += (uint32_t)wave_sum(lp);
           }
           S.nact += ncand;
           planned -= ncand;
@@ -1165,7 +1207,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
               kv_block = true;
             } else {
               const int G = min(nie, kp);
-              const int na = admit_first(t, G, true, adm, adm_len, adm_minlen);
+              const int na = admit_first(t, G, true, adm, adm_minlen);
               free_empty = nie - na;
               if (na < G) kv_block = true;
             }
@@ -1174,8 +1216,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       }
     }
     if (adm > 0) {
-      S.sum_s += (int64_t)adm * t;
-      S.sum_comp += (int64_t)adm * t + adm_len;
+      S.sum_s += (uint32_t)adm * (uint32_t)t;
+      mac(S.sum_start, (uint32_t)adm, (uint32_t)t);
       S.min_end = min(S.min_end, t + adm_minlen);
       if (nact0 == 0) S.min_s = t;
       S.max_s = t;
@@ -1242,6 +1284,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
               const int v0 = __shfl(v[0], (q >> 1) & (WAVE - 1));
               const int v1 = __shfl(v[1], (q >> 1) & (WAVE - 1));
               return (q & 1) ? v1 : v0;
+            }
+          };
+          auto at_job_u = [&](const int(&v)[K], int j) -> int {  // j uniform
+            if constexpr (K == 1) {
+              return readlane(v[0], j);
+            } else {
+              const int v0 = readlane(v[0], j & (WAVE - 1)), v1 = readlane(v[1], j & (WAVE - 1));
+              return (j >> 6) ? v1 : v0;
             }
           };
           auto at_pos_u = [&](const int(&v)[K], int q) -> int {  // q uniform
@@ -1347,13 +1397,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
               rr[k] = run;
             }
             const int rbase = wave_scan_incl(run) - run;
-            const int64_t bud0 = (int64_t)M - S.res;
+            const int bud0 = M - S.res;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
               const int q = lane * K + k;
               int v = min(Gq, Beff - N + q + 1);
               if (M != 0) {
-                const int64_t b = bud0 + rbase + rr[k];
+                const int64_t b = (int64_t)bud0 + rbase + rr[k];
                 const int bb = b < 0 ? -1 : (b >= (int64_t)IDLE ? IDLE - 1 : (int)b);
                 int lo = 0;  // queued jobs whose summed reservations fit
 #pragma unroll
@@ -1456,11 +1506,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
           const int A_m = p_m >= 0 ? at_pos_u(ap, p_m) : 0;
           // spans after each counted event, with the jobs at the positions
           // above and the admitted jobs 0..A-1
-          int64_t qE = 0, qSM = 0, qSSM = 0, qX = 0, qP = 0;
-          int qU = 0;
-          int64_t &lE = DEFER ? pE : qE, &lSM = DEFER ? pSM : qSM, &lSSM = DEFER ? pSSM : qSSM,
-                  &lX = DEFER ? pX : qX, &lP = DEFER ? pP : qP;
-          int& lU = DEFER ? pU : qU;
+          SpanSums here;
+          here.clear();
+          SpanSums& sums = DEFER ? lane_sums : here;
           int lmx = 0, lma = 0;
           {
             int cg = xs_g, cg_max = xs_max, cg_min = xs_min;
@@ -1474,22 +1522,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
               const int saA = at_job(sa, max(A - 1, 0)), sgA = at_job(sg, max(A - 1, 0));
               if (((gem >> k) & 1u) & (q <= p_m)) {
                 const int Er = q == p_m ? tau_rel : e_nx;
-                const int64_t D = (int64_t)(Er - e);
-                const int64_t so = N - 1 - q, s = so + A;
-                const int min_s = t - cg_max;
-                const int max_s = A > 0 ? t + sgA : t - cg_min;
-                const int64_t sum_s = s * (int64_t)t - cg + (A > 0 ? saA : 0);
-                const int64_t m0 = (int64_t)(t + e - min_s) + 1;
-                const int64_t sm = D * m0 + D * (D - 1) / 2;
-                lE += D * (sum_s - s * (int64_t)min_s);
-                lSM += sm;
-                lSSM += s * sm;
-                const int ext = max_s - min_s;
-                lX += D * ext;
-                if (ext > alpha) lU += (int)D;
-                lP = max(lP, s * (int64_t)(t + Er) - sum_s);
+                // starts relative to t: -cg_max the earliest, sgA (of the last
+                // admitted job) or -cg_min the latest
+                const int s = N - 1 - q + A;
+                const int ext = (A > 0 ? sgA : -cg_min) + cg_max;
+                sums.add((uint32_t)(Er - e), (uint32_t)s, (uint32_t)(e + cg_max + 1),
+                         (uint32_t)(s * cg_max - cg + (A > 0 ? saA : 0)), ext, alpha);
                 lmx = max(lmx, ext);
-                lma = max(lma, (int)s);
+                lma = max(lma, s);
               }
               if (vq) {
                 cg += dg[k];
@@ -1500,38 +1540,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
           }
           // span [t, first event): the jobs active now
           {
-            const int64_t D = (int64_t)(p_m >= 0 ? e_first : tau_rel), s = N;
-            const int64_t m0 = (int64_t)(t - S.min_s) + 1;
-            const int64_t sm = D * m0 + D * (D - 1) / 2;
-            acc_E += D * (S.sum_s - s * (int64_t)S.min_s);
-            acc_SM += sm;
-            acc_SSM += s * sm;
             const int ext = S.max_s - S.min_s;
-            acc_ext += D * ext;
-            if (ext > alpha) acc_unfair += D;
-            acc_peak = max(acc_peak, s * (int64_t)(t + D) - S.sum_s);
+            acc.add((uint32_t)(p_m >= 0 ? e_first : tau_rel), (uint32_t)N,
+                    (uint32_t)(t - S.min_s + 1), S.sum_s - (uint32_t)N * (uint32_t)S.min_s, ext,
+                    alpha);
             lmx = max(lmx, ext);
             lma = max(lma, N);
           }
-          if constexpr (!DEFER) {
-            acc_E += wave_sum64(lE);
-            acc_SM += wave_sum64(lSM);
-            acc_SSM += wave_sum64(lSSM);
-            acc_ext += wave_sum64(lX);
-            acc_unfair += wave_sum(lU);
-            acc_peak = max(acc_peak, wave_max64(lP));
-          }
-          acc_busy += (int64_t)tau_rel;
+          if constexpr (!DEFER) reduce_lane_sums(here);
+          acc_busy += tau_rel;
           acc_maxext = max(acc_maxext, wave_max(lmx));
           acc_maxact = max(acc_maxact, wave_max(lma));
-          // completions of the admitted jobs
-          {
-            int lsc = 0;
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-              if (k * WAVE + lane < A_m) lsc += sg[k] + qlen[k];
-            S.sum_comp += (int64_t)A_m * t + wave_sum(lsc);
-          }
+          // starts of the admitted jobs
+          mac(S.sum_start, (uint32_t)A_m, (uint32_t)t);
+          if (A_m > 0) S.sum_start += (uint32_t)at_job_u(sa, A_m - 1);
           // retire every job done by tau, then seat the admitted ones that are
           // still running
           const int tau = t + tau_rel;
@@ -1576,13 +1598,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
           S.ndone += wave_sum(lret);
           {
             int cnt = 0, lres = 0, mn = IDLE, mx = -1, me = IDLE;
-            int64_t ss = 0;
+            uint32_t ss = 0;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
               if (ws_end[k] != IDLE) {
                 cnt++;
                 lres += ws_end[k] - ws_start[k];
-                ss += ws_start[k];
+                ss += (uint32_t)ws_start[k];
                 mn = min(mn, ws_start[k]);
                 mx = max(mx, ws_start[k]);
                 me = min(me, ws_end[k]);
@@ -1590,7 +1612,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
             }
             S.nact = wave_sum(cnt);
             S.res = wave_sum(lres);
-            S.sum_s = wave_sum64(ss);
+            S.sum_s = (uint32_t)wave_sum((int)ss);
             S.min_s = S.nact > 0 ? wave_min(mn) : IDLE;
             S.max_s = S.nact > 0 ? wave_max(mx) : -1;
             S.min_end = wave_min(me);
@@ -1677,11 +1699,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       const int gbits = 32 - __builtin_clz((uint32_t)(t - S.min_s) | 1u);
       const bool packed = gbits < 32 && (int64_t)maxlen < (int64_t)(0xFFFFFFFFu >> gbits);
       int stop = 0, e0 = 0, st_g = 0, st_gmax = -1, st_gmin = IDLE, tau_end = 0;
-      int64_t qE = 0, qSM = 0, qSSM = 0, qX = 0, qP = 0;
-      int qU = 0;
-      int64_t &lE = DEFER ? pE : qE, &lSM = DEFER ? pSM : qSM, &lSSM = DEFER ? pSSM : qSSM,
-              &lX = DEFER ? pX : qX, &lP = DEFER ? pP : qP;
-      int& lU = DEFER ? pU : qU;
+      SpanSums here;
+      here.clear();
+      SpanSums& sums = DEFER ? lane_sums : here;
       // Sort the N completions into KS registers per lane (position
       // p = lane * KS + k holds the p-th) and account the spans.  KS = K sorts
       // every slot in place; KS = 1 first packs up to 64 active slots into one
@@ -1786,19 +1806,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
             const int e = t + (int)dk[k];
             const int e_next = (k + 1 < KS) ? t + (int)dk[k + 1 < KS ? k + 1 : k] : e_up;
             if (valid & (pos < stop) & (e_next > e)) {
-              const int64_t D = (int64_t)(e_next - e);
-              const int64_t s = N - 1 - pos;
-              const int min_s = t - cg_max, max_s = t - cg_min;
-              const int64_t sum_s = s * (int64_t)t - cg;
-              const int64_t m0 = (int64_t)(e - min_s) + 1;
-              const int64_t sm = D * m0 + D * (D - 1) / 2;
-              lE += D * (sum_s - s * (int64_t)min_s);
-              lSM += sm;
-              lSSM += s * sm;
-              const int ext = max_s - min_s;
-              lX += D * ext;
-              if (ext > alpha) lU += (int)D;
-              lP = max(lP, s * (int64_t)e_next - sum_s);
+              const int s = N - 1 - pos;
+              sums.add((uint32_t)(e_next - e), (uint32_t)s, (uint32_t)(e - t + cg_max + 1),
+                       (uint32_t)(s * cg_max - cg), cg_max - cg_min, alpha);
             }
             if (pos == stop) {
               sg = cg;
@@ -1831,28 +1841,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       // span [t, e_0): every job still active; the set only shrinks after it,
       // so it also carries the largest extent and count of the sweep
       {
-        const int64_t D = (int64_t)(e0 - t), s = N;
-        const int64_t m0 = (int64_t)(t - S.min_s) + 1;
-        const int64_t sm = D * m0 + D * (D - 1) / 2;
-        acc_E += D * (S.sum_s - s * (int64_t)S.min_s);
-        acc_SM += sm;
-        acc_SSM += s * sm;
         const int ext = S.max_s - S.min_s;
-        acc_ext += D * ext;
-        if (ext > alpha) acc_unfair += D;
-        acc_peak = max(acc_peak, s * (int64_t)e0 - S.sum_s);
+        acc.add((uint32_t)(e0 - t), (uint32_t)N, (uint32_t)(t - S.min_s + 1),
+                S.sum_s - (uint32_t)N * (uint32_t)S.min_s, ext, alpha);
         acc_maxext = max(acc_maxext, ext);
         acc_maxact = max(acc_maxact, N);
       }
-      if constexpr (!DEFER) {
-        acc_E += wave_sum64(lE);
-        acc_SM += wave_sum64(lSM);
-        acc_SSM += wave_sum64(lSSM);
-        acc_ext += wave_sum64(lX);
-        acc_unfair += wave_sum(lU);
-        acc_peak = max(acc_peak, wave_max64(lP));
-      }
-      acc_busy += (int64_t)(tau_end - t);
+      if constexpr (!DEFER) reduce_lane_sums(here);
+      acc_busy += tau_end - t;
       if (POL == POL_ISJL && amax_sweep && mode == 0) {
         // Phase TWO switches to DRAIN at the first event before tau_end with an
         // idle worker that has nothing planned (from its first completion, or
@@ -1904,7 +1900,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       S.nact = N - nret;
       S.min_end = wave_min(me);
       if (S.nact > 0) {
-        S.sum_s = (int64_t)S.nact * t - st_g;
+        S.sum_s = (uint32_t)S.nact * (uint32_t)t - (uint32_t)st_g;
         S.min_s = t - st_gmax;
         S.max_s = t - st_gmin;
       } else {
@@ -1951,7 +1947,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
         if ((r >> 6) != chunk) load_chunk(r >> 6);
         const int off = r & (WAVE - 1);
         const bool in = (lane >= off) & (rel_t < tn);
-        const bool m = in && rel_r < hr && S.res + (int64_t)plen(W[rel_r]) <= M;
+        const bool m = in && rel_r < hr && S.res + plen(W[rel_r]) <= M;
         const uint64_t mm = ballot(m);
         if (mm) {
           tn = min(tn, readlane(rel_t, __builtin_ctzll(mm)));
@@ -1985,42 +1981,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
     }
 
     // (6) account steps t .. tn-1 (Section 5)
-    const int64_t D = (int64_t)(tn - t);
     if (S.nact != 0) {
-      const int64_t s = S.nact;
       // largest footprint at step t (it grows by one per step of the span) and
       // the span's externality: each active job pays the largest footprint
       // minus its own, a constant over the span
-      int64_t m0, xe;
-      if (PRE) {
-        m0 = (int64_t)t + S.G + 1;
-        xe = s * (int64_t)S.G - (S.sp - S.sum_s);
-      } else {
-        m0 = (int64_t)(t - S.min_s) + 1;
-        xe = S.sum_s - s * (int64_t)S.min_s;
-      }
-      const int64_t sm = D * m0 + D * (D - 1) / 2;
-      acc_E += D * xe;
-      acc_SM += sm;
-      acc_SSM += s * sm;
+      const uint32_t s = (uint32_t)S.nact;
+      const uint32_t m0 = PRE ? (uint32_t)(t + S.G + 1) : (uint32_t)(t - S.min_s + 1);
+      const uint32_t xe = PRE ? s * (uint32_t)S.G - (S.sp - S.sum_s)
+                              : S.sum_s - s * (uint32_t)S.min_s;
       const int ext = S.max_s - S.min_s;
-      acc_ext += D * ext;
-      acc_busy += D;
-      if (ext > alpha) acc_unfair += D;
+      acc.add((uint32_t)(tn - t), s, m0, xe, ext, alpha);
+      acc_busy += tn - t;
       acc_maxext = max(acc_maxext, ext);
       acc_maxact = max(acc_maxact, S.nact);
-      acc_peak = max(acc_peak, s * (int64_t)tn - S.sum_s + (PRE ? S.sp : 0));
     }
     S.t = tn;
   }
-  if constexpr (DEFER) {
-    acc_E += wave_sum64(pE);
-    acc_SM += wave_sum64(pSM);
-    acc_SSM += wave_sum64(pSSM);
-    acc_ext += wave_sum64(pX);
-    acc_unfair += wave_sum(pU);
-    acc_peak = max(acc_peak, wave_max64(pP));
-  }
+  if constexpr (DEFER) reduce_lane_sums(lane_sums);
 
   if (failed) {
     write_marker(a.out, a.out_T, inst, T_INTERNAL, lane);
@@ -2033,15 +2010,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
     m.T = S.t;
     m.O = osum;
     m.Q = qsum;
-    m.E = acc_E;
-    m.C = a.c * (int64_t)S.t + a.tau * acc_SSM;
-    m.W = a.c * (int64_t)S.t + a.tau * acc_SM;
-    m.sum_completion = S.sum_comp;
-    m.sum_latency = S.sum_comp - rsum;
-    m.sum_extent = acc_ext;
+    const int64_t sum_comp = (int64_t)S.sum_start + lsum;
+    m.E = (int64_t)acc.E;
+    m.C = a.c * (int64_t)S.t + a.tau * (int64_t)(acc.SSM2 >> 1);  // both sums are even
+    m.W = a.c * (int64_t)S.t + a.tau * (int64_t)(acc.SM2 >> 1);
+    m.sum_completion = sum_comp;
+    m.sum_latency = sum_comp - rsum;
+    m.sum_extent = (int64_t)acc.X;
     m.busy_steps = acc_busy;
-    m.peak_kv = acc_peak;
-    m.unfair_steps = acc_unfair;
+    m.peak_kv = acc.peak;
+    m.unfair_steps = acc.unfair;
     m.max_extent = acc_maxext;
     m.max_active = acc_maxact;
     a.out[inst] = m;
