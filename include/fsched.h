@@ -224,7 +224,10 @@ int fsched_cost_decompose(const fsched_params* p, int64_t n_inst, int32_t n_jobs
  * reservations within M_kv unless a job runs alone, and |s_i - s_j| <= alpha for
  * every pair active at a common step.  Exhaustive search over schedules in start
  * order with a memo and lower bounds, started from the ISJL schedule of the
- * instance (which is returned when nothing beats it).  A first pass keeps the
+ * instance (which is returned when nothing beats it).  With B = 2 and every
+ * arrival 0 a dynamic program over (started jobs, running job, its progress)
+ * takes the search's place where its table fits the LDS, with the same results.
+ * A first pass of the search keeps the
  * search's memo in LDS and stops a search after 2^22 steps; the searches it
  * stops are run again by a second pass with a memo of 2^20 entries per wave in
  * device scratch (256 MiB from the library's pool, with the instance list;

@@ -524,13 +524,10 @@ int fsched_bruteforce_opt(const fsched_params* p, int64_t n_inst, int32_t n_jobs
   a.B = (p->B == 0 || p->B > n_jobs) ? n_jobs : p->B;
   a.alpha = p->alpha;
   a.M = p->M_kv;
-  a.wave_words = (int32_t)fs::opt_lds_words_per_wave();
-  const int wpb = 1;
-  const size_t lds = (size_t)a.wave_words * 4 * wpb;
-  // Scratch of the second pass (searches the first pass's LDS memo could not
-  // finish): the list of their instances, two counters and a memo region per
+  // Scratch of the later passes: the counters, the lists of the instances that
+  // each pass leaves to the next, and the second search pass's memo region per
   // wave, from the library's pool (else the device's default pool).
-  const size_t list_bytes = round256((size_t)n_inst * 4 + 8);
+  const size_t list_bytes = 256 + round256((size_t)n_inst * 4 * fs::OPT_LISTS);
   const size_t memo_bytes = (size_t)fs::OPT_FB_WAVES * fs::OPT_FB_MEMO_ENTRIES * 16;
   void* fb = nullptr;
   {
@@ -556,15 +553,11 @@ int fsched_bruteforce_opt(const fsched_params* p, int64_t n_inst, int32_t n_jobs
     a.T = dT;
     a.start = dS;
     if (fb) {
-      a.fb_count = (int32_t*)fb;
-      a.fb_list = (int32_t*)fb + 2;
+      a.counters = (int32_t*)fb;
+      a.lists = (int32_t*)((char*)fb + 256);
       a.fb_memo = (uint32_t*)((char*)fb + list_bytes);
-      hipError_t e = hipMemsetAsync(a.fb_count, 0, 8, s);
-      if (e != hipSuccess) return hip_fail(e);
     }
-    hipError_t e = fs::launch_opt(a, wpb, lds, s);
-    if (e == hipSuccess && fb)
-      e = fs::launch_opt_fallback(a, fs::opt_fallback_lds_words_per_wave() * 4, s);
+    hipError_t e = fs::launch_opt(a, s);
     return e == hipSuccess ? FSCHED_OK : hip_fail(e);
   };
   auto release_fb = [&]() {

@@ -29,6 +29,8 @@
 // k = c % 8) and pick the next one with a wave minimum over packed keys
 // (lb << 16 | d << 3 | k); the memo is an LDS hash table probed 64 slots at a
 // time; the DFS stack and the per-frame candidate keys live in LDS.
+#include <algorithm>
+
 #include "opt_common.hpp"
 #include "wave.hpp"
 
@@ -43,6 +45,8 @@ constexpr int FW = 8;                 // words per frame
 constexpr int CACHE = 192;            // cached candidate keys per frame (3 per lane)
 constexpr uint32_t NOKEY = 0xFFFFFFFFu;
 constexpr int GUARD = 1 << 22;        // DFS pushes per search in the first pass
+constexpr int PAIR_ENTRIES = 7680;       // two-worker tables: first launch (15 KB)
+constexpr int PAIR_ENTRIES_MAX = 32000;  // second launch (64 KB)
 
 // frame word offsets
 enum { F_S = 0, F_SIG, F_PLO, F_PHI, F_BOUND, F_BEST, F_THR, F_FLAGS };
@@ -509,33 +513,351 @@ __device__ bool solve(const OptArgs& a, int64_t inst, const Inst& I, Memo& memo,
   return true;
 }
 
-}  // namespace
+// Claim the next entry of a list (counters[0] entries, counters[1] the claim
+// counter): its instance, or -1 once the list is exhausted.
+__device__ __forceinline__ int64_t claim(const int32_t* list, int32_t* counters, int nlist,
+                                         int lane) {
+  int idx = 0;
+  if (lane == 0) idx = atomicAdd(counters + 1, 1);
+  idx = readlane(idx, 0);
+  return idx < nlist ? (int64_t)list[idx] : -1;
+}
 
-__global__ __launch_bounds__(256) void opt_kernel(OptArgs a) {
-  extern __shared__ uint32_t lds_raw[];
-  const int wib = threadIdx.x >> 6;
-  const int64_t inst = (int64_t)blockIdx.x * (blockDim.x >> 6) + wib;
-  if (inst >= a.n_inst) return;
-  const int lane = lane_id();
-  uint32_t* base = lds_raw + (size_t)wib * (size_t)a.wave_words;
-  uint32_t* frames = base + MEMO_BYTES / 4;
-  uint32_t* keys = frames + FRAMES * FW;
+__device__ __forceinline__ void append(int32_t* list, int32_t* counters, int64_t inst, int lane) {
+  if (lane == 0) list[atomicAdd(counters, 1)] = (int32_t)inst;
+}
 
-  if (a.T[inst] < 0) return;  // ISJL's error marker
-  Inst I;
-  if (!load_inst(a, inst, lane, I)) return;
-  Memo memo{base, I.compact, false, I.compact ? MEMO_BYTES / 8 : MEMO_BYTES / 16};
-  memo.clear(lane);
-  if (!solve(a, inst, I, memo, frames, keys, lane, GUARD)) {
-    // the LDS memo was too small for this search: leave it to the second pass
-    if (lane == 0) {
-      if (a.fb_list) {
-        const int slot = atomicAdd(a.fb_count, 1);
-        a.fb_list[slot] = (int32_t)inst;
-      } else {
-        a.T[inst] = FSCHED_T_INTERNAL;
+// Two workers, every job released at step 0: dynamic program over
+//   W(S, s, q)  least remaining time when the jobs S have started and only s
+//               runs, with progress q (the other worker is idle)
+//   E(S)        the same with both workers idle
+// A start of k beside s at progress q needs q <= alpha and the pair within the
+// KV budget; then the shorter remainder ends first, which is again a state of
+// this kind, so with r = len_s - q, t = min(r, len_k) and S' = S + k
+//   W0(S, s, q) = min over k of t + W(S', survivor, its progress)   (start now)
+//   W(S, s, q)  = min(W0(S, s, q) if q <= alpha, 1 + W(S, s, q + 1)),
+//   W(S, s, len_s) = E(S),  E(S) = min over k of W(S', k, 0),  E(all) = 0,
+// and beyond alpha W is len_s - q + E(S), which is not stored.  Identical jobs
+// are one class, so S is a mixed-radix number of started jobs per class (a
+// superset has the larger number) and s a class: at most 256 rows of
+// 1 + sum of min(alpha + 1, len) entries of 16 bits.
+//
+// The search above visits these states one at a time through its memo, about
+// 1.6 M vector instructions per tiny instance at one wave per SIMD (its memo
+// fills the LDS); the table has a few thousand entries, each 8 candidates, and
+// every entry of one level (number of started jobs) is independent of the
+// others, one (S, s) per lane, its q from the largest down.  65,536 tiny
+// instances (n = 8, alpha = 2, M_kv = 16): 656 -> 1.8 ms with the ISJL launch
+// (0.47 ms) included; 3,000 at alpha = 19, M_kv = 24: 9.0 s -> 1.0 ms.
+struct PairDp {
+  const Inst& I;
+  uint16_t* tab;     // rows of R entries: E(S), then W(S, s, 0..qmax_s) per class
+  uint8_t* order;    // rows by number of started jobs, the most first
+  uint16_t* info;    // per row: classes with a job left | classes started << 8
+  uint32_t* cls;     // per class (by its first job): len | offset of its entries << 16
+  int lane;
+  int C, NS, R;
+  uint32_t reps;     // first jobs of the classes, 4 bits each
+  uint32_t first;    // bit j: job j is the first of its class
+  int cnt[NMAX], stride[NMAX], off[NMAX];
+
+  __device__ int qmax(int len) const { return min(I.alpha, len - 1); }
+
+  // Row and class tables; false when the rows do not fit `entries`.
+  __device__ bool setup(int entries) {
+    C = 0;
+    NS = 1;
+    R = 1;
+    reps = first = 0;
+#pragma unroll
+    for (int j = 0; j < NMAX; ++j) {
+      cnt[j] = stride[j] = off[j] = 0;
+      if (j < I.n && I.eqprev[j] == 0u) {
+        int m = 0;
+#pragma unroll
+        for (int i = 0; i < NMAX; ++i) m += i < I.n && I.len[i] == I.len[j] ? 1 : 0;
+        cnt[j] = m;
+        stride[j] = NS;
+        off[j] = R;
+        NS *= m + 1;
+        R += qmax(I.len[j]) + 1;
+        reps |= (uint32_t)j << (4 * C);
+        first |= 1u << j;
+        C++;
       }
     }
+    if (NS * R > entries) return false;
+#pragma unroll
+    for (int j = 0; j < NMAX; ++j)
+      if (lane == j) cls[j] = (uint32_t)I.len[j] | ((uint32_t)off[j] << 16);
+    return true;
+  }
+
+  __device__ int fill() {
+    // the digits of row r, its class masks, and its place in the level order
+    int lev[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = i * WAVE + lane;
+      lev[i] = -1;
+      if (i * WAVE < NS) {
+        int rest = r, l = 0;
+        uint32_t left = 0, started = 0;
+#pragma unroll
+        for (int j = NMAX - 1; j >= 0; --j) {
+          if ((first >> j) & 1u) {
+            // rest < 256 and stride <= 128: the product is exact
+            const int dgt = (int)(((uint32_t)rest * (uint32_t)((65536 + stride[j] - 1) / stride[j])) >> 16);
+            rest -= dgt * stride[j];
+            l += dgt;
+            if (dgt < cnt[j]) left |= 1u << j;
+            if (dgt > 0) started |= 1u << j;
+          }
+        }
+        if (r < NS) {
+          lev[i] = l;
+          info[r] = (uint16_t)(left | (started << 8));
+        }
+      }
+    }
+    int begin = 0;
+    for (int L = I.n; L >= 0; --L) {
+      int end = begin;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (i * WAVE < NS) {
+          const uint64_t m = ballot(lev[i] == L);
+          if (lev[i] == L) order[end + mbcnt(m)] = (uint8_t)(i * WAVE + lane);
+          end += __builtin_popcountll(m);
+        }
+      }
+      wave_lds_sync();
+      // one (row, class) per lane; 65536 / C rounded up is exact for products below 2^12
+      const int items = L > 0 ? (end - begin) * C : 1;
+      const uint32_t inv = (65536u + (uint32_t)C - 1u) / (uint32_t)C;
+      for (int it0 = 0; it0 < items; it0 += WAVE) {
+        const int it = it0 + lane;
+        const int ro = (int)(((uint32_t)it * inv) >> 16);
+        const bool in = it < items;
+        const int S = in ? order[begin + ro] : 0;
+        const int c = (int)((reps >> (4 * (it - ro * C))) & 7u);
+        const uint32_t w = in ? info[S] : 0u;
+        const uint32_t cw = cls[c];
+        const int len = (int)(cw & 0xFFFFu), co = (int)(cw >> 16);
+        const int row = S * R;
+        const bool on = in & (((w >> (8 + c)) & 1u) != 0u);
+        int E = L == I.n ? 0 : 0x7FFF;
+#pragma unroll
+        for (int k = 0; k < NMAX; ++k)
+          if (((first >> k) & 1u) && ((w >> k) & 1u))
+            E = min(E, (int)tab[row + stride[k] * R + off[k]]);
+        // every lane of a row finds the same value
+        if (in) tab[row] = (uint16_t)E;
+        const int qm = on ? qmax(len) : -1;
+        int best = len - qm + E - 1;
+        const int qtop = wave_max(qm);
+        for (int q = qtop; q >= 0; --q) {
+          if (q <= qm) {
+            best++;
+            const int r = len - q;
+#pragma unroll
+            for (int k = 0; k < NMAX; ++k) {
+              if (((first >> k) & 1u) && ((w >> k) & 1u) &
+                                             ((I.M == 0) | (len + I.len[k] <= I.M))) {
+                const int d = r - I.len[k];
+                const int t = min(r, I.len[k]);
+                const int qq = d > 0 ? q + I.len[k] : r;  // the survivor's progress
+                const bool emp = (d == 0) | (qq > I.alpha);
+                const int at = emp ? 0 : (d > 0 ? co : off[k]) + qq;
+                const int v = (int)tab[row + stride[k] * R + at] + t + (emp ? abs(d) : 0);
+                best = min(best, v);
+              }
+            }
+            tab[row + co + q] = (uint16_t)best;
+          }
+        }
+      }
+      wave_lds_sync();
+      begin = end;
+    }
+    return (int)tab[0];
+  }
+
+  // Value of the state right after k started in the row of `row` (k counted in
+  // it), beside job j (-1: none) at progress p.
+  __device__ int after_start(int row, int k, int j, int p) const {
+    const uint32_t ck = cls[k];
+    const int lk = (int)(ck & 0xFFFFu);
+    int sl = lk, so = (int)(ck >> 16), qq = 0, t = 0;
+    if (j >= 0) {
+      const uint32_t cj = cls[j];
+      const int r = (int)(cj & 0xFFFFu) - p;
+      t = min(r, lk);
+      if (r > lk) {
+        sl = (int)(cj & 0xFFFFu);
+        so = (int)(cj >> 16);
+        qq = p + lk;
+      } else {
+        qq = r;
+      }
+    }
+    if (qq >= sl || qq > I.alpha) return t + (sl - qq) + (int)tab[row * R];
+    return t + (int)tab[row * R + so + qq];
+  }
+};
+
+// Solve instance `inst` by the two-worker table: false when it is not of that
+// kind or its table does not fit `entries`.  The schedule is the one that the
+// search's reconstruction gives: from each state the first candidate in key
+// order that attains the state's value.
+__device__ bool solve_pair(const OptArgs& a, int64_t inst, const Inst& I, uint16_t* tab,
+                           int entries, uint8_t* order, uint16_t* info, uint32_t* cls, int lane) {
+  if (I.B != 2 || I.rmax != 0) return false;
+  const int bound = (int)a.T[inst];
+  {
+    // nothing beats a makespan at the root's lower bound: the longest job, the
+    // jobs that fit beside no other one, and half of the rest
+    int sum = 0, alone = 0, maxl = 0;
+#pragma unroll
+    for (int j = 0; j < NMAX; ++j) {
+      if (j < I.n) {
+        sum += I.len[j];
+        maxl = max(maxl, I.len[j]);
+        if (I.compat[j] == 0u) alone += I.len[j];
+      }
+    }
+    if (bound <= max(maxl, alone + (sum - alone + 1) / 2)) return true;
+  }
+  PairDp dp{I, tab, order, info, cls, lane};
+  if (!dp.setup(entries)) return false;
+  wave_lds_sync();
+  const int v = uni(dp.fill());
+  if (v >= bound) return true;
+  if (lane == 0) a.T[inst] = v;
+  if (!a.start) return true;
+  const int64_t row = inst * (int64_t)a.n;
+  const uint32_t none = 0xFFFFFFFFu;
+  uint32_t S = 0u, plo = none, phi = none;
+  int sig = 0, val = v, at = 0;  // at: the row of S
+  for (int step = 0; step < I.n; ++step) {
+    int maxrem = 0, sumU = 0;
+#pragma unroll
+    for (int j = 0; j < NMAX; ++j) {
+      const int p = prog_of(plo, phi, j);
+      if (p != 0xFF) maxrem = max(maxrem, I.len[j] - p);
+      if (j < I.n && !((S >> j) & 1u)) sumU += I.len[j];
+    }
+    uint32_t best = NOKEY;
+    for (int c0 = 0; c0 < (maxrem + 1) * 8; c0 += WAVE) {
+      const int c = c0 + lane, d = c >> 3, k = c & 7;
+      const uint32_t key = cand_key(I, S, sig, plo, phi, c, maxrem, sumU);
+      if (key != NOKEY) {
+        int j = -1, pj = 0, kc = k, rk = at;
+#pragma unroll
+        for (int i = 0; i < NMAX; ++i) {
+          const int p = prog_of(plo, phi, i);
+          if (p != 0xFF && I.len[i] - p > d) {
+            j = I.eqprev[i] ? __builtin_ctz(I.eqprev[i]) : i;
+            pj = p + d;
+          }
+          if (i == k && I.eqprev[i]) kc = __builtin_ctz(I.eqprev[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < NMAX; ++i)
+          if (i == kc) rk += dp.stride[i];
+        if (d + dp.after_start(rk, kc, j, pj) == val) best = min(best, key);
+      }
+    }
+    best = wave_umin(best);
+    if (best == NOKEY) break;  // not reachable: some candidate attains the value
+    const int d = (int)((best >> 3) & 0x1FFFu), k = (int)(best & 7u);
+    uint32_t nlo = 0, nhi = 0;
+#pragma unroll
+    for (int j = 0; j < NMAX; ++j) {
+      const int p = prog_of(plo, phi, j);
+      int q = 0xFF;
+      if (j == k) {
+        q = 0;
+        const int kc = I.eqprev[j] ? __builtin_ctz(I.eqprev[j]) : j;
+#pragma unroll
+        for (int i = 0; i < NMAX; ++i)
+          if (i == kc) at += dp.stride[i];
+      } else if (p != 0xFF && I.len[j] - p > d) {
+        q = p + d;
+      }
+      if (j < 4) nlo |= (uint32_t)q << (8 * j);
+      else nhi |= (uint32_t)q << (8 * (j - 4));
+    }
+    if (lane == 0) a.start[row + k] = sig + d;
+    S |= 1u << k;
+    sig += d;
+    plo = nlo;
+    phi = nhi;
+    val -= d;
+  }
+  return true;
+}
+
+}  // namespace
+
+// Two-worker instances without releases, one wave (one block) per instance of
+// the batch or of src's list; what it does not solve goes to dst's list.
+__global__ __launch_bounds__(64) void opt_pair_kernel(OptArgs a, int entries, int32_t* src,
+                                                      int32_t* src_n, int32_t* dst,
+                                                      int32_t* dst_n) {
+  extern __shared__ uint32_t lds_raw[];
+  const int lane = lane_id();
+  uint32_t* cls = lds_raw;
+  uint16_t* info = (uint16_t*)(cls + NMAX);
+  uint8_t* order = (uint8_t*)(info + 256);
+  uint16_t* tab = (uint16_t*)(order + 256);
+  const int nlist =
+      src ? __hip_atomic_load(src_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  int64_t inst = blockIdx.x;
+  while (true) {
+    if (src) inst = claim(src, src_n, nlist, lane);
+    if (inst < 0) break;
+    Inst I;
+    if (a.T[inst] >= 0 && load_inst(a, inst, lane, I)) {
+      if (!solve_pair(a, inst, I, tab, entries, order, info, cls, lane))
+        append(dst, dst_n, inst, lane);
+    }
+    if (!src) break;
+  }
+}
+
+// The list counters start at zero (a kernel rather than a memset, which a
+// captured graph would not replay reliably).
+__global__ __launch_bounds__(64) void opt_clear_kernel(int32_t* counters, int n) {
+  if ((int)threadIdx.x < n) counters[threadIdx.x] = 0;
+}
+
+// One wave per instance of the batch, or (with todo_list) waves that take the
+// listed instances one at a time until the list is exhausted.
+__global__ __launch_bounds__(64) void opt_kernel(OptArgs a) {
+  extern __shared__ uint32_t lds_raw[];
+  const int lane = lane_id();
+  uint32_t* base = lds_raw;
+  uint32_t* frames = base + MEMO_BYTES / 4;
+  uint32_t* keys = frames + FRAMES * FW;
+  const int nlist = a.todo_list ? __hip_atomic_load(a.todo_count, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT)
+                                : 0;
+  int64_t inst = blockIdx.x;
+  while (true) {
+    if (a.todo_list) inst = claim(a.todo_list, a.todo_count, nlist, lane);
+    if (inst < 0) break;
+    Inst I;
+    if (a.T[inst] >= 0 /* else ISJL's error marker */ && load_inst(a, inst, lane, I)) {
+      Memo memo{base, I.compact, false, I.compact ? MEMO_BYTES / 8 : MEMO_BYTES / 16};
+      memo.clear(lane);
+      if (!solve(a, inst, I, memo, frames, keys, lane, GUARD)) {
+        // the LDS memo was too small for this search: leave it to the second pass
+        if (a.fb_list) append(a.fb_list, a.fb_count, inst, lane);
+        else if (lane == 0) a.T[inst] = FSCHED_T_INTERNAL;
+      }
+    }
+    if (!a.todo_list) break;
   }
 }
 
@@ -552,11 +874,8 @@ __global__ __launch_bounds__(64) void opt_fallback_kernel(OptArgs a) {
   Memo memo{a.fb_memo + (size_t)blockIdx.x * 4 * (size_t)OPT_FB_MEMO_ENTRIES, false, true,
             OPT_FB_MEMO_ENTRIES};
   while (true) {
-    int idx = 0;
-    if (lane == 0) idx = atomicAdd(a.fb_count + 1, 1);
-    idx = readlane(idx, 0);
-    if (idx >= nlist) break;
-    const int64_t inst = a.fb_list[idx];
+    const int64_t inst = claim(a.fb_list, a.fb_count, nlist, lane);
+    if (inst < 0) break;
     Inst I;
     if (!load_inst(a, inst, lane, I)) continue;
     memo.clear(lane);
@@ -565,20 +884,72 @@ __global__ __launch_bounds__(64) void opt_fallback_kernel(OptArgs a) {
   }
 }
 
-hipError_t launch_opt(const OptArgs& a, int wpb, size_t lds, hipStream_t s) {
-  const int64_t blocks = (a.n_inst + wpb - 1) / wpb;
-  hipLaunchKernelGGL(opt_kernel, dim3((unsigned)blocks), dim3((unsigned)(wpb * WAVE)), lds, s, a);
+static size_t opt_lds_words_per_wave() { return MEMO_BYTES / 4 + FRAMES * FW + FRAMES * CACHE; }
+
+static size_t opt_fallback_lds_words_per_wave() { return FRAMES * FW + FRAMES * CACHE; }
+
+namespace {
+
+// Bytes of the two-worker kernel's LDS beside its table.
+constexpr size_t PAIR_LDS_FIXED = NMAX * 4 + 256 * 2 + 256;
+
+hipError_t launch_pair(const OptArgs& a, int64_t blocks, int entries, int32_t* src, int32_t* src_n,
+                       int32_t* dst, int32_t* dst_n, hipStream_t s) {
+  hipLaunchKernelGGL(opt_pair_kernel, dim3((unsigned)blocks), dim3((unsigned)WAVE),
+                     PAIR_LDS_FIXED + ((size_t)entries * 2 + 3) / 4 * 4, s, a, entries, src, src_n,
+                     dst, dst_n);
   return hipGetLastError();
 }
 
-hipError_t launch_opt_fallback(const OptArgs& a, size_t lds, hipStream_t s) {
-  hipLaunchKernelGGL(opt_fallback_kernel, dim3((unsigned)OPT_FB_WAVES), dim3((unsigned)WAVE), lds,
-                     s, a);
+}  // namespace
+
+hipError_t launch_opt(const OptArgs& a0, hipStream_t s) {
+  OptArgs a = a0;
+  const size_t lds = (size_t)opt_lds_words_per_wave() * 4;
+  int64_t blocks = a.n_inst;
+  if (a.lists) {
+    hipLaunchKernelGGL(opt_clear_kernel, dim3(1), dim3((unsigned)WAVE), 0, s, a.counters,
+                       OPT_COUNTERS);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    a.fb_list = a.lists;
+    a.fb_count = a.counters;
+    if (a.B == 2) {
+      // Tables of up to 2^n rows of 1 + n (alpha + 1) entries.  The first launch
+      // takes those within PAIR_ENTRIES (10 waves share a CU's LDS then; 65,536
+      // instances at alpha = 2 took 1.82 ms with it, 1.87 / 1.98 / 3.07 ms with
+      // limits of 5,120 / 4,096 / 2,560 entries, which leave more to the second
+      // launch); a second one those within PAIR_ENTRIES_MAX, when a table can be
+      // larger at all.
+      const int64_t per_job = (int64_t)std::min(a.alpha, OPT_LEN_LIMIT - 1) + 1;
+      const int64_t worst = ((int64_t)1 << a.n) * (1 + a.n * per_job);
+      const int first = (int)std::min<int64_t>(worst, PAIR_ENTRIES);
+      int32_t* list = a.lists + a.n_inst;
+      int32_t* list_n = a.counters + 2;
+      e = launch_pair(a, a.n_inst, first, nullptr, nullptr, list, list_n, s);
+      if (e != hipSuccess) return e;
+      if (worst > PAIR_ENTRIES) {
+        int32_t* list2 = list + a.n_inst;
+        int32_t* list2_n = a.counters + 4;
+        e = launch_pair(a, std::min<int64_t>(a.n_inst, 1024),
+                        (int)std::min<int64_t>(worst, PAIR_ENTRIES_MAX), list, list_n, list2,
+                        list2_n, s);
+        if (e != hipSuccess) return e;
+        list = list2;
+        list_n = list2_n;
+      }
+      // the search takes what is left (releases, larger tables)
+      a.todo_list = list;
+      a.todo_count = list_n;
+      blocks = std::min<int64_t>(a.n_inst, 1024);  // the waves that its LDS lets run at once
+    }
+  }
+  hipLaunchKernelGGL(opt_kernel, dim3((unsigned)blocks), dim3((unsigned)WAVE), lds, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !a.lists) return e;
+  hipLaunchKernelGGL(opt_fallback_kernel, dim3((unsigned)OPT_FB_WAVES), dim3((unsigned)WAVE),
+                     opt_fallback_lds_words_per_wave() * 4, s, a);
   return hipGetLastError();
 }
-
-size_t opt_lds_words_per_wave() { return MEMO_BYTES / 4 + FRAMES * FW + FRAMES * CACHE; }
-
-size_t opt_fallback_lds_words_per_wave() { return FRAMES * FW + FRAMES * CACHE; }
 
 }  // namespace fs

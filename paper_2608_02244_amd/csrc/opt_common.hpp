@@ -16,31 +16,38 @@ struct OptArgs {
   int32_t n;
   int32_t B;          // effective capacity (n when unlimited)
   int32_t alpha;      // INT32_MAX = infinite
-  int32_t wave_words;
   int64_t M;          // 0 = no KV budget
   const int32_t* arrival;
   const int32_t* prompt;
   const int32_t* output;
   int64_t* T;         // in: ISJL makespan (incumbent) or marker; out: optimum
   int32_t* start;     // in: ISJL schedule; out: an optimal schedule (nullable)
-  // Second pass for the searches that reach the first pass's step cap: the
-  // first pass appends their instance indices to fb_list (fb_count[0] of
-  // them; fb_count[1] is the claim counter of the second pass, both zero
-  // before the first pass) and the second pass solves them again with a large
-  // memo in fb_memo (OPT_FB_WAVES regions of OPT_FB_MEMO_ENTRIES 16-byte
-  // entries).  Null fb_list: a capped search reports FSCHED_T_INTERNAL.
+  // Scratch for the searches that one launch leaves to the next: OPT_LISTS lists
+  // of n_inst instance indices, OPT_COUNTERS counters (per list its length and
+  // the claim counter of the launch that takes it) and the second search pass's
+  // memo (OPT_FB_WAVES regions of OPT_FB_MEMO_ENTRIES 16-byte entries).  Null
+  // lists: one search launch over the batch, and a capped search reports
+  // FSCHED_T_INTERNAL.
+  int32_t* lists;
+  int32_t* counters;
+  uint32_t* fb_memo;
+  // Set by launch_opt: the list that the search takes (null: the whole batch),
+  // and the list of the searches that reach the first pass's step cap, which the
+  // second pass solves again with its large memo.
+  int32_t* todo_list;
+  int32_t* todo_count;
   int32_t* fb_list;
   int32_t* fb_count;
-  uint32_t* fb_memo;
 };
 
+constexpr int OPT_LISTS = 3;
+constexpr int OPT_COUNTERS = 2 * OPT_LISTS;
 constexpr int OPT_FB_WAVES = 16;                // waves of the second pass
 constexpr int OPT_FB_MEMO_ENTRIES = 1 << 20;    // memo entries per wave (16 MiB)
 constexpr int OPT_FB_GUARD = 1 << 28;           // DFS pushes per search in the second pass
 
-hipError_t launch_opt(const OptArgs& a, int waves_per_block, size_t lds_bytes, hipStream_t s);
-hipError_t launch_opt_fallback(const OptArgs& a, size_t lds_bytes, hipStream_t s);
-size_t opt_lds_words_per_wave();
-size_t opt_fallback_lds_words_per_wave();
+// The two-worker tables, the search and its second pass (a.T and a.start hold
+// the incumbent).
+hipError_t launch_opt(const OptArgs& a, hipStream_t s);
 
 }  // namespace fs

@@ -8,6 +8,7 @@ import pytest
 
 import oracle
 from oracle import ALPHA_INF
+from test_gpu_opt import check as check_opt
 from test_gpu_simulate import assert_same, dev, gpu_sim, log  # noqa: F401  (dev: the fixture)
 
 pytestmark = pytest.mark.gpu
@@ -46,3 +47,40 @@ def test_largest_reservations_and_footprints(dev, policy, n, B, alpha, M_kv, pre
         p[1] = p[1] // 64  # a shorter instance beside it, where the starts spread further
     check(dev, f"{policy} n={n} B={B} M={M_kv} prefill={prefill}", a, p, o, prefill=prefill,
           policy=policy, B=B, alpha=alpha, M_kv=M_kv, cost_c=3, cost_tau=2)
+
+
+@pytest.mark.parametrize("n,top,alphas", [
+    (1, 9, (0, 3)), (2, 255, (0, 1, 254, ALPHA_INF)), (3, 255, (0, 100, ALPHA_INF)),
+    (5, 60, (0, 7, 59)), (7, 24, (1, 23)), (8, 1, (0, 4)), (8, 3, (0, 2, 5)),
+    (8, 16, (0, 1, 2, 4, 11, 19, ALPHA_INF)),
+])
+def test_two_worker_optima(dev, n, top, alphas):
+    """The two-worker table of the exact optimum: one class of identical jobs to eight
+    different ones, tables from a few entries to beyond the largest that it keeps
+    (the search takes those), instances with a release (not its kind) among them."""
+    rng = np.random.default_rng(100 * n + top)
+    size = (70, n)
+    z = np.zeros(size, np.int32)
+    o = rng.integers(1, top + 1, size=size).astype(np.int32)
+    o[::7] = rng.integers(1, top + 1, size=(10, 1))  # identical jobs
+    if n == 8 and top == 16:
+        o[3] = 13 + np.arange(8)
+    a = z.copy()
+    a[5::9, -1] = 3
+    for alpha in alphas:
+        for M in (0, max(2, (3 * top) // 2)):
+            check_opt(dev, f"n={n} top={top} alpha={alpha} M={M}", a, z, o, B=2, alpha=alpha,
+                      M_kv=M)
+
+
+def test_two_worker_tables_beyond_lds(dev):
+    """Eight long jobs of different lengths: 2^8 rows of up to 2,000 entries, more than the
+    table keeps, solved by the search beside short instances solved by the table."""
+    rng = np.random.default_rng(8)
+    o = np.concatenate([rng.integers(120, 136, size=(2, 8)), rng.integers(1, 5, size=(30, 8)),
+                        rng.integers(17, 21, size=(4, 8))]).astype(np.int32)
+    z = np.zeros_like(o)
+    # alpha = 130: the long instances need 256 * (1 + 8 * 131) entries at most; M_kv lets no
+    # two long jobs run together, so their search ends at once
+    T = check_opt(dev, "long", z, z, o, B=2, alpha=130, M_kv=200)
+    assert (T[:2] == o[:2].sum(1)).all()
