@@ -255,43 +255,37 @@ int launch_simulate(const fsched_params* p, int64_t n_inst, int32_t n, const int
     }
   }
 
-  hipError_t err = hipSuccess;
-  for (int general = 0; general < 2 && err == hipSuccess; ++general) {
-    fs::SimArgs b = a;
-    b.off_arr = NP;
-    b.off_q = NP + (general ? NP : 0);
-    b.off_stage = b.off_q + q_words;
-    b.wave_words = b.off_stage + stage_words;
-    b.wave_words = (b.wave_words + 3) & ~3;
-    size_t per_wave = (size_t)b.wave_words * 4;
-    int wpb = 4;
-    while (wpb > 1 && per_wave * wpb > 64 * 1024) wpb >>= 1;
-    size_t lds = per_wave * wpb;
-    hipError_t e;
-    const bool pre = (p->flags & FSCHED_F_PREFILL) != 0;
-    switch (p->policy) {
-      case FSCHED_FCFS:
-        e = pre ? fs::launch_sim_fcfs_prefill(b, K, NW, general, wpb, lds, s)
-                : fs::launch_sim_fcfs(b, K, NW, general, wpb, lds, s);
-        break;
-      case FSCHED_LJF:
-        e = pre ? fs::launch_sim_ljf_prefill(b, K, NW, general, wpb, lds, s)
-                : fs::launch_sim_ljf(b, K, NW, general, wpb, lds, s);
-        break;
-      case FSCHED_ISJL:
-        if (upper)
-          e = pre ? fs::launch_sim_isjl_robust_prefill(b, K, NW, general, wpb, lds, s)
-                  : fs::launch_sim_isjl_robust(b, K, NW, general, wpb, lds, s);
-        else
-          e = pre ? fs::launch_sim_isjl_prefill(b, K, NW, general, wpb, lds, s)
-                  : fs::launch_sim_isjl(b, K, NW, general, wpb, lds, s);
-        break;
-      default:
-        e = pre ? fs::launch_sim_sjf_prefill(b, K, NW, general, wpb, lds, s)
-                : fs::launch_sim_sjf(b, K, NW, general, wpb, lds, s);
-        break;
-    }
-    err = e;
+  a.off_q = NP;
+  a.off_stage = a.off_q + q_words;
+  a.wave_words = a.off_stage + stage_words;
+  a.wave_words = (a.wave_words + 3) & ~3;
+  size_t per_wave = (size_t)a.wave_words * 4;
+  int wpb = 4;
+  while (wpb > 1 && per_wave * wpb > 64 * 1024) wpb >>= 1;
+  size_t lds = per_wave * wpb;
+  hipError_t err;
+  const bool pre = (p->flags & FSCHED_F_PREFILL) != 0;
+  switch (p->policy) {
+    case FSCHED_FCFS:
+      err = pre ? fs::launch_sim_fcfs_prefill(a, K, NW, wpb, lds, s)
+              : fs::launch_sim_fcfs(a, K, NW, wpb, lds, s);
+      break;
+    case FSCHED_LJF:
+      err = pre ? fs::launch_sim_ljf_prefill(a, K, NW, wpb, lds, s)
+              : fs::launch_sim_ljf(a, K, NW, wpb, lds, s);
+      break;
+    case FSCHED_ISJL:
+      if (upper)
+        err = pre ? fs::launch_sim_isjl_robust_prefill(a, K, NW, wpb, lds, s)
+                : fs::launch_sim_isjl_robust(a, K, NW, wpb, lds, s);
+      else
+        err = pre ? fs::launch_sim_isjl_prefill(a, K, NW, wpb, lds, s)
+                : fs::launch_sim_isjl(a, K, NW, wpb, lds, s);
+      break;
+    default:
+      err = pre ? fs::launch_sim_sjf_prefill(a, K, NW, wpb, lds, s)
+              : fs::launch_sim_sjf(a, K, NW, wpb, lds, s);
+      break;
   }
   release(a.rank);
   release(a.qlink);

@@ -8,7 +8,6 @@
 namespace fs {
 
 // Per-instance markers written into metrics.T (besides the public ones).
-constexpr int64_t T_DEFERRED = -100;  // arrivals not sorted: the general kernel finishes it
 constexpr int64_t T_INTERNAL = -7;    // the event loop found no next event (internal error)
 
 // Kernel limits.
@@ -27,7 +26,6 @@ struct SimArgs {
   int64_t c, tau;
   int32_t NP;         // n rounded up to a power of two (>= 64)
   int32_t wave_words; // LDS words per wave
-  int32_t off_arr;    // word offset of arrival-by-rank (general kernel)
   int32_t off_q;      // word offset of the plan-queue links (ISJL)
   int32_t off_stage;  // word offset of the gather / release buffer (not FCFS)
   int32_t resume;     // ISJL: Phase TWO resumes once A_max <= alpha (1) or waits
@@ -40,8 +38,8 @@ struct SimArgs {
   int64_t* out_T;       // when non-null: only the makespan (or marker) per instance
   int32_t* start;
   int32_t* finish;
-  // Scratch: rank of every job in the priority order, written by the
-  // sorted-arrival kernel once it has sorted and read back at each release
+  // Scratch: rank of every job in the priority order, by release position,
+  // written once the instance has been sorted and read back at each release
   // chunk (rows of rank_stride entries, a multiple of 64 so that no 128-byte
   // line is shared by two instances).  Required for every policy but FCFS.
   uint16_t* rank;
@@ -54,29 +52,28 @@ struct SimArgs {
   int32_t q_stride;
 };
 
-// Chooses and launches the kernel instantiation for one policy.  `general`
-// selects the variant for instances whose arrivals are not sorted by index.
-hipError_t launch_sim_fcfs(const SimArgs& a, int K, int NW, bool general, int waves_per_block,
+// Chooses and launches the kernel instantiation for one policy.
+hipError_t launch_sim_fcfs(const SimArgs& a, int K, int NW, int waves_per_block,
                            size_t lds_bytes, hipStream_t s);
-hipError_t launch_sim_ljf(const SimArgs& a, int K, int NW, bool general, int waves_per_block,
+hipError_t launch_sim_ljf(const SimArgs& a, int K, int NW, int waves_per_block,
                           size_t lds_bytes, hipStream_t s);
-hipError_t launch_sim_isjl(const SimArgs& a, int K, int NW, bool general, int waves_per_block,
+hipError_t launch_sim_isjl(const SimArgs& a, int K, int NW, int waves_per_block,
                            size_t lds_bytes, hipStream_t s);
 // Robust-ISJL (Section 3.4): ISJL planning on prompt + upper[i].
-hipError_t launch_sim_isjl_robust(const SimArgs& a, int K, int NW, bool general,
-                                  int waves_per_block, size_t lds_bytes, hipStream_t s);
+hipError_t launch_sim_isjl_robust(const SimArgs& a, int K, int NW, int waves_per_block,
+                                  size_t lds_bytes, hipStream_t s);
 // The prefill-at-admission variant of each policy (and of Robust-ISJL).
-hipError_t launch_sim_fcfs_prefill(const SimArgs& a, int K, int NW, bool general,
-                                   int waves_per_block, size_t lds_bytes, hipStream_t s);
-hipError_t launch_sim_ljf_prefill(const SimArgs& a, int K, int NW, bool general,
-                                  int waves_per_block, size_t lds_bytes, hipStream_t s);
-hipError_t launch_sim_isjl_prefill(const SimArgs& a, int K, int NW, bool general,
-                                   int waves_per_block, size_t lds_bytes, hipStream_t s);
-hipError_t launch_sim_sjf_prefill(const SimArgs& a, int K, int NW, bool general,
-                                  int waves_per_block, size_t lds_bytes, hipStream_t s);
-hipError_t launch_sim_isjl_robust_prefill(const SimArgs& a, int K, int NW, bool general,
-                                          int waves_per_block, size_t lds_bytes, hipStream_t s);
-hipError_t launch_sim_sjf(const SimArgs& a, int K, int NW, bool general, int waves_per_block,
+hipError_t launch_sim_fcfs_prefill(const SimArgs& a, int K, int NW, int waves_per_block,
+                                   size_t lds_bytes, hipStream_t s);
+hipError_t launch_sim_ljf_prefill(const SimArgs& a, int K, int NW, int waves_per_block,
+                                  size_t lds_bytes, hipStream_t s);
+hipError_t launch_sim_isjl_prefill(const SimArgs& a, int K, int NW, int waves_per_block,
+                                   size_t lds_bytes, hipStream_t s);
+hipError_t launch_sim_sjf_prefill(const SimArgs& a, int K, int NW, int waves_per_block,
+                                  size_t lds_bytes, hipStream_t s);
+hipError_t launch_sim_isjl_robust_prefill(const SimArgs& a, int K, int NW, int waves_per_block,
+                                          size_t lds_bytes, hipStream_t s);
+hipError_t launch_sim_sjf(const SimArgs& a, int K, int NW, int waves_per_block,
                           size_t lds_bytes, hipStream_t s);
 
 }  // namespace fs

@@ -3,8 +3,8 @@
 #include "sim_kernel.hpp"
 
 namespace fs {
-hipError_t launch_sim_isjl(const SimArgs& a, int K, int NW, bool general, int waves_per_block,
-                         size_t lds_bytes, hipStream_t s) {
-  return launch_sim<POL_ISJL>(a, K, NW, general, waves_per_block, lds_bytes, s);
+hipError_t launch_sim_isjl(const SimArgs& a, int K, int NW, int waves_per_block,
+                           size_t lds_bytes, hipStream_t s) {
+  return launch_sim<POL_ISJL>(a, K, NW, waves_per_block, lds_bytes, s);
 }
 }  // namespace fs

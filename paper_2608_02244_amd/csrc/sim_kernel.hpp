@@ -25,7 +25,6 @@
 //
 // Per-wave state:
 //   LDS   W[r]     jobs in the policy's priority order, packed (len << 12 | id)
-//         ARR[r]   arrival of rank r (general variant only)
 //         QN[r]    next job in the same ISJL plan queue (uint16, ISJL)
 //         STG[j]   gather buffer of the first queued ranks (uint16, not FCFS)
 //         PEND[i]  released ranks on their way into the bitmap (aliases STG)
@@ -53,22 +52,23 @@ constexpr uint32_t LMASK = 0xFFFFFu;
 __device__ __forceinline__ int plen(uint32_t w) { return (int)(w >> 12); }
 __device__ __forceinline__ int pid(uint32_t w) { return (int)(w & 0xFFFu); }
 
-// Bitonic sort of NP (power of two) keys in LDS, ascending, by one wave.
-__device__ inline void wave_bitonic_sort(uint32_t* W, int NP, int lane) {
-  for (int k = 2; k <= NP; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = lane; i < (NP >> 1); i += WAVE) {
-        int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-        int hi = lo + j;
-        bool up = (lo & k) == 0;
-        uint32_t x = W[lo], y = W[hi];
-        if ((x > y) == up) {
-          W[lo] = y;
-          W[hi] = x;
-        }
-      }
-      wave_lds_sync();
-    }
+// Release order of jobs whose arrivals are not sorted by index: RK[i] holds the
+// rank of job i on entry and the rank of the i-th released job afterwards (n
+// entries, arrivals below 2^20).  Every load of the row has returned before the
+// sort ends, so it is rewritten in place.
+template <int KS>
+__device__ inline void release_order(const int32_t* A, uint16_t* RK, int n, int lane) {
+  uint32_t key[KS];
+#pragma unroll
+  for (int k = 0; k < KS; ++k) {
+    const int i = k * WAVE + lane;
+    key[k] = i < n ? ((uint32_t)A[i] << 12) | RK[i] : 0xFFFFFFFFu;
+  }
+  reg_sort_keys<KS, true>(key, lane);
+#pragma unroll
+  for (int k = 0; k < KS; ++k) {
+    const int i = lane * KS + k;
+    if (i < n) RK[i] = (uint16_t)(key[k] & 0xFFFu);
   }
 }
 
@@ -196,7 +196,7 @@ struct SpanSums {
 // scratch (else in LDS).  Every kernel with up to 8 slots per lane but FCFS's
 // is held to 128 VGPRs, so that 4 waves share a SIMD where the LDS allows 16
 // per CU (FCFS's 4- and 8-slot kernels ran slower that way and keep 3).
-template <int POL, int K, int NW, bool GEN, bool ROB, bool PRE, bool FILL, bool QH = false,
+template <int POL, int K, int NW, bool ROB, bool PRE, bool FILL, bool QH = false,
           bool FAIR = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <= 2 || (K <= 8 && POL != POL_FCFS) ? 4 : (K <= 8 ? 3 : 1)))) void simulate_kernel(SimArgs a) {
   static_assert(!ROB || POL == POL_ISJL, "predicted sizes: ISJL only");
@@ -215,7 +215,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   const int lane = lane_id();
   const int n = a.n;
   uint32_t* W = lds_raw + (size_t)wib * (size_t)a.wave_words;
-  int32_t* ARR = (int32_t*)(W + a.off_arr);
   uint16_t* QN = (uint16_t*)(W + a.off_q);
   // ISJL with up to 8 slots per lane: the plan-queue links live in HBM scratch
   // when that lets more waves share a CU (agent-scope accesses, so one lane's
@@ -247,18 +246,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   // KV reservation of job j planned with size `plan`
   auto resv_len = [&](int j, int plan) -> int { return PRE ? P[j] + plan : plan; };
 
-  if (GEN) {  // only instances the sorted-arrival kernel deferred
-    const int64_t prev = a.out_T ? a.out_T[inst] : a.out[inst].T;
-    if (prev != T_DEFERRED) return;
-  }
-
   // ---- load, validate, instance constants --------------------------------
   // One pass over the job table: validation, instance totals and the
   // priority keys (LJF / ISJL: (-len, index); SJF: (len, index); FCFS:
-  // (arrival, index), or (len, index) in arrival order when arrivals are
-  // sorted); padding keys sort last.
+  // (len, index) in job order, which is its release order when the arrivals
+  // are sorted); padding keys sort last.
   const int NP = a.NP;
-  int bad = 0, big = 0, unsorted = 0, maxlen = 0, maxfoot = 0, maxarr = 0;
+  int bad = 0, big = 0, late = 0, maxlen = 0, maxfoot = 0, maxarr = 0;
   int64_t osum = 0, qsum = 0, rsum = 0;
   int64_t lsum = 0;  // PRE: summed service length (else osum)
   uint64_t q2 = 0;  // twice the footprint sum Q: one 32 x 32 -> 64 product per job
@@ -304,7 +298,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       const int64_t plan_len = PRE ? (int64_t)u : (int64_t)p + (int64_t)u;
       const int64_t foot = (int64_t)p + (int64_t)u;
       big |= (foot >= LEN_LIMIT);
-      unsorted |= (prev > ar);
+      late |= (prev > ar);
       if (foot < LEN_LIMIT && len > maxlen) maxlen = (int)len;
       if (foot < LEN_LIMIT && foot > maxfoot) maxfoot = (int)foot;
       if (ar > maxarr) maxarr = ar;
@@ -319,8 +313,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       if (PRE) lsum += o;
       const uint32_t l32 = (uint32_t)(ROB ? plan_len : len) & LMASK;
       if (POL == POL_LJF || POL == POL_ISJL) key = ((LMASK - l32) << 12) | (uint32_t)i;
-      else if (POL == POL_SJF) key = (l32 << 12) | (uint32_t)i;
-      else if (GEN) key = (((uint32_t)ar & LMASK) << 12) | (uint32_t)i;
       else key = (l32 << 12) | (uint32_t)i;
     }
     W[i] = key;
@@ -328,17 +320,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   }
   bad = ballot(bad != 0) != 0;
   big = ballot(big != 0) != 0;
-  unsorted = ballot(unsorted != 0) != 0;
+  const bool unsorted = ballot(late != 0) != 0;  // the arrivals are not sorted by job index
   if (bad) {
     write_marker(a.out, a.out_T, inst, FSCHED_T_INVALID, lane);
     return;
   }
   if (big) {
     write_marker(a.out, a.out_T, inst, FSCHED_T_TOOLARGE, lane);
-    return;
-  }
-  if (!GEN && unsorted) {
-    write_marker(a.out, a.out_T, inst, T_DEFERRED, lane);
     return;
   }
   maxlen = wave_max(maxlen);
@@ -348,7 +336,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   qsum = (int64_t)((uint64_t)wave_sum64((int64_t)q2) >> 1);  // every term is even
   rsum = wave_sum64(rsum);
   lsum = PRE ? wave_sum64(lsum) : osum;
-  if (GEN && maxarr >= ARR_LIMIT) {
+  if (unsorted && maxarr >= ARR_LIMIT) {
     write_marker(a.out, a.out_T, inst, FSCHED_T_TOOLARGE, lane);
     return;
   }
@@ -370,21 +358,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   }
 
   // ---- priority order -----------------------------------------------------
-  if (!(POL == POL_FCFS && !GEN)) {
+  uint16_t* RK = POL != POL_FCFS ? a.rank + inst * (int64_t)a.rank_stride : nullptr;
+  if (POL == POL_FCFS && unsorted) {  // FCFS's order is the release order
+    for (int i = lane; i < NP; i += WAVE)
+      W[i] = i < n ? ((uint32_t)A[i] << 12) | (uint32_t)i : 0xFFFFFFFFu;
+  }
+  if (POL != POL_FCFS || unsorted) {
     wave_lds_sync();
-    switch (NP) {
-      case 64: wave_reg_sort<1, true>(W, lane); break;
-      case 128: wave_reg_sort<2, true>(W, lane); break;
-      case 256: wave_reg_sort<4, true>(W, lane); break;
-      case 512: wave_reg_sort<8, true>(W, lane); break;
-      case 1024: wave_reg_sort<16, true>(W, lane); break;
-      case 2048: wave_reg_sort<32, true>(W, lane); break;
-      default: wave_bitonic_sort(W, NP, lane); break;
+    if constexpr (NW == 2) {  // more than 2,048 jobs
+      wave_reg_sort<64, true>(W, lane);
+    } else {
+      switch (NP) {
+        case 64: wave_reg_sort<1, true>(W, lane); break;
+        case 128: wave_reg_sort<2, true>(W, lane); break;
+        case 256: wave_reg_sort<4, true>(W, lane); break;
+        case 512: wave_reg_sort<8, true>(W, lane); break;
+        case 1024: wave_reg_sort<16, true>(W, lane); break;
+        default: wave_reg_sort<32, true>(W, lane); break;
+      }
     }
     wave_lds_sync();
-    // sorted-arrival kernel: each job's rank goes to the rank table for the
-    // release chunks (only this wave touches its row)
-    uint16_t* RKw = (!GEN && POL != POL_FCFS) ? a.rank + inst * (int64_t)a.rank_stride : nullptr;
+    // each job's rank goes to the rank table for the release chunks (only this
+    // wave touches its row)
     for (int r = lane; r < n; r += WAVE) {
       uint32_t key = W[r];
       int id = (int)(key & 0xFFFu);
@@ -393,10 +388,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       else if (POL == POL_SJF) len = key >> 12;
       else len = (uint32_t)(PRE ? O[id] : P[id] + O[id]);
       W[r] = (len << 12) | (uint32_t)id;
-      if (GEN) ARR[r] = A[id];
-      else if (RKw) RKw[id] = (uint16_t)r;
+      if (POL != POL_FCFS) RK[id] = (uint16_t)r;
     }
-    if (RKw) __threadfence_block();  // the stores complete before the row is read
+  }
+  if (POL != POL_FCFS) {
+    __threadfence_block();  // the stores complete before the row is read
+    if (unsorted) {
+      // the table is put in release order: one more sort per instance, after
+      // which releases are taken a chunk at a time as with sorted arrivals
+      // (4,095 x 1,333 ISJL at B = 64 in random job order: 0.35 ms; a second
+      // launch that searched the unreleased ranks at every release took 0.87)
+      if constexpr (NW == 2) {  // more than 2,048 jobs
+        release_order<64>(A, RK, n, lane);
+      } else {
+        switch (NP) {
+          case 64: release_order<1>(A, RK, n, lane); break;
+          case 128: release_order<2>(A, RK, n, lane); break;
+          case 256: release_order<4>(A, RK, n, lane); break;
+          case 512: release_order<8>(A, RK, n, lane); break;
+          case 1024: release_order<16>(A, RK, n, lane); break;
+          default: release_order<32>(A, RK, n, lane); break;
+        }
+      }
+      __threadfence_block();
+    }
   }
   wave_lds_sync();
 
@@ -423,23 +438,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   }
   PoolBits<NW> pool;
   pool.clear_all();
-  PoolBits<NW> unrel;  // general variant, non-FCFS: ranks not yet released
-  unrel.clear_all();
-  if (GEN && POL != POL_FCFS) {
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      int base = (i * WAVE + lane) << 5;
-      uint32_t m = 0u;
-      if (base + 32 <= n) m = 0xFFFFFFFFu;
-      else if (base < n) m = (1u << (n - base)) - 1u;
-      unrel.w[i] = m;
-    }
-  }
   int relk = 0;           // release cursor
   int qcount = 0;         // queued jobs: released, not admitted, not planned
   int chunk = -1;         // release chunk loaded in rel_t / rel_r
   int rel_t = IDLE, rel_r = 0;
-  int next_rel = 0;       // general variant, non-FCFS
   int head = 0;           // FCFS: first waiting rank
   // ISJL
   int mode = 0;           // 0 FILL, 1 DRAIN
@@ -486,21 +488,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   int iter = 0;
   bool failed = false;
 
-  // rank of each job in the priority order (sorted-arrival kernel, not FCFS)
-  const uint16_t* RK =
-      (!GEN && POL != POL_FCFS) ? a.rank + inst * (int64_t)a.rank_stride : nullptr;
-  // Load release chunk `c` (64 consecutive jobs in arrival order; the general
-  // variant releases through ARR and loads chunks only under FCFS).
+  // Load release chunk `c`: 64 consecutive jobs in release order.
   auto load_chunk = [&](int c) {
-    int j = c * WAVE + lane;
+    const int j = c * WAVE + lane;
     rel_t = IDLE;
     rel_r = 0;
     if (POL == POL_FCFS) {
-      if (j < n) rel_t = GEN ? ARR[j] : A[j];
+      if (j < n) rel_t = A[unsorted ? pid(W[j]) : j];
       rel_r = j;
     } else if (j < n) {
-      rel_t = A[j];
       rel_r = RK[j];
+      rel_t = A[unsorted ? pid(W[rel_r]) : j];
     }
     chunk = c;
   };
@@ -761,11 +759,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
     }
     if (S.ndone == n) break;
 
-    // (2) releases.  Arrivals are non-decreasing in job order here, so the
-    // jobs released by t are the next lanes of the loaded chunk up to the
-    // first later arrival; their pool bits are scattered with LDS atomics and
-    // folded into the register bitmap once.
-    if (POL == POL_FCFS || !GEN) {
+    // (2) releases.  The jobs released by t are the next lanes of the loaded
+    // chunk up to the first later arrival; their pool bits are scattered with
+    // LDS atomics and folded into the register bitmap once.
+    {
       bool any = false;
       while (relk < n) {
         if ((relk >> 6) != chunk) load_chunk(relk >> 6);
@@ -791,25 +788,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
         for (int i = 0; i < NW; ++i) pool.w[i] |= PEND[i * WAVE + lane];
         wave_lds_sync();
       }
-    } else if (next_rel <= t) {
-      int nr = IDLE, ng = 0;
-#pragma unroll
-      for (int i = 0; i < NW; ++i) {
-        uint32_t u = unrel.w[i], got = 0u;
-        int base = (i * WAVE + lane) << 5;
-        while (u) {
-          int b = __builtin_ctz(u);
-          u &= u - 1u;
-          int ar = ARR[base + b];
-          if (ar <= t) got |= 1u << b;
-          else nr = min(nr, ar);
-        }
-        unrel.w[i] &= ~got;
-        pool.w[i] |= got;
-        ng += __builtin_popcount(got);
-      }
-      qcount += wave_sum(ng);
-      next_rel = wave_min(nr);
     }
 
     // (3) A_max(t): largest progress among the jobs still active
@@ -1245,13 +1223,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       const int Qn = POL == POL_FCFS ? relk - head : qcount;
       if (S.nact >= 2 && Qn > 0 && (POL != POL_ISJL || (mode == 0 && planned == 0))) {
         int H = IDLE;  // next release
-        if (POL == POL_FCFS || !GEN) {
-          if (relk < n) {
-            if ((relk >> 6) != chunk) load_chunk(relk >> 6);
-            H = readlane(rel_t, relk & (WAVE - 1));
-          }
-        } else {
-          H = next_rel;
+        if (relk < n) {
+          if ((relk >> 6) != chunk) load_chunk(relk >> 6);
+          H = readlane(rel_t, relk & (WAVE - 1));
         }
         // taken when a few completions come before the first queued job could
         // finish after being admitted at the first of them (ISJL: and before
@@ -1649,13 +1623,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
         (POL == POL_FCFS ? head == relk
                          : (qcount == 0 && (POL != POL_ISJL || (mode == 0 && planned == 0))))) {
       int r_next = IDLE;
-      if (POL == POL_FCFS || !GEN) {
-        if (relk < n) {
-          if ((relk >> 6) != chunk) load_chunk(relk >> 6);
-          r_next = readlane(rel_t, relk & (WAVE - 1));
-        }
-      } else {
-        r_next = next_rel;
+      if (relk < n) {
+        if ((relk >> 6) != chunk) load_chunk(relk >> 6);
+        r_next = readlane(rel_t, relk & (WAVE - 1));
       }
       if (S.min_end <= r_next) {
 #pragma unroll
@@ -1872,13 +1842,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
         int tn_queued = IDLE;
         if (qcount > 0) {
           tn_queued = t;
-        } else if (POL == POL_FCFS || !GEN) {
-          if (relk < n) {
-            if ((relk >> 6) != chunk) load_chunk(relk >> 6);
-            tn_queued = readlane(rel_t, relk & (WAVE - 1));
-          }
-        } else {
-          tn_queued = next_rel;
+        } else if (relk < n) {
+          if ((relk >> 6) != chunk) load_chunk(relk >> 6);
+          tn_queued = readlane(rel_t, relk & (WAVE - 1));
         }
         if (max(tn_free, tn_queued) < tau_end) mode = 1;
       }
@@ -1936,7 +1902,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
     // precedes that head in the policy's order and fits beside the running jobs;
     // the first such arrival bounds the span.
     const bool blocked_head =
-        !GEN && !PRE && !ROB && qcount > 0 && S.nact > 0 &&
+        !PRE && !ROB && qcount > 0 && S.nact > 0 &&
         ((POL == POL_SJF && S.nact < Beff) ||
          (POL == POL_ISJL && K <= 2 && mode == 0 && free_empty > 0 && kv_block));
     if (blocked_head) {
@@ -1957,15 +1923,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
         r = (r & ~(WAVE - 1)) + WAVE;
       }
     }
-    if (rel_matters) {
-      if (POL == POL_FCFS || !GEN) {
-        if (relk < n) {
-          if ((relk >> 6) != chunk) load_chunk(relk >> 6);
-          tn = min(tn, readlane(rel_t, relk & 63));
-        }
-      } else {
-        tn = min(tn, next_rel);
-      }
+    if (rel_matters && relk < n) {
+      if ((relk >> 6) != chunk) load_chunk(relk >> 6);
+      tn = min(tn, readlane(rel_t, relk & 63));
     }
     if (POL == POL_ISJL) {
       if (planned > 0 && t_w1 > t) {
@@ -2044,8 +2004,7 @@ inline bool resident_at_once(const void* kern, int64_t blocks, int wpb, size_t l
 // exceeds it).  With a finite budget ISJL's completions mostly meet the guard
 // one at a time, and its event loop runs faster without the sweep's code.
 template <int POL, bool ROB = false, bool PRE = false>
-hipError_t launch_sim(const SimArgs& a, int K, int NW, bool general, int wpb, size_t lds,
-                      hipStream_t s) {
+hipError_t launch_sim(const SimArgs& a, int K, int NW, int wpb, size_t lds, hipStream_t s) {
   const int64_t blocks = (a.n_inst + wpb - 1) / wpb;
   dim3 grid((unsigned)blocks), block((unsigned)(wpb * WAVE));
   constexpr bool FILL_OK = !ROB && !PRE && POL != POL_LJF;
@@ -2055,23 +2014,21 @@ hipError_t launch_sim(const SimArgs& a, int K, int NW, bool general, int wpb, si
   // lane; the fill-sweep kernels run with alpha at least every length, so
   // nothing is planned there)
   const bool qh = POL == POL_ISJL && K <= 8 && !fill && a.qlink != nullptr;
-#define FS_LAUNCH(KK, NN, GG, FF, QQ)                                                     \
-  if (K == KK && NW == NN && general == GG && fill == FF && qh == QQ) {                   \
-    if constexpr (!GG && KK <= 8) {                                                       \
-      if (resident_at_once((const void*)simulate_kernel<POL, KK, NN, GG, ROB, PRE, FF, QQ, true>, \
+#define FS_LAUNCH(KK, NN, FF, QQ)                                                         \
+  if (K == KK && NW == NN && fill == FF && qh == QQ) {                                    \
+    if constexpr (KK <= 8) {                                                              \
+      if (resident_at_once((const void*)simulate_kernel<POL, KK, NN, ROB, PRE, FF, QQ, true>, \
                            blocks, wpb, lds)) {                                           \
-        hipLaunchKernelGGL((simulate_kernel<POL, KK, NN, GG, ROB, PRE, FF, QQ, true>), grid, block, \
+        hipLaunchKernelGGL((simulate_kernel<POL, KK, NN, ROB, PRE, FF, QQ, true>), grid, block, \
                            lds, s, a);                                                    \
         return hipGetLastError();                                                         \
       }                                                                                   \
     }                                                                                     \
-    hipLaunchKernelGGL((simulate_kernel<POL, KK, NN, GG, ROB, PRE, FF, QQ>), grid, block, lds, \
-                       s, a);                                                             \
+    hipLaunchKernelGGL((simulate_kernel<POL, KK, NN, ROB, PRE, FF, QQ>), grid, block, lds, s, \
+                       a);                                                                \
     return hipGetLastError();                                                             \
   }
-#define FS_LAUNCH_K(KK, FF, QQ)                                                             \
-  FS_LAUNCH(KK, 1, false, FF, QQ) FS_LAUNCH(KK, 2, false, FF, QQ) FS_LAUNCH(KK, 1, true, FF, QQ) \
-  FS_LAUNCH(KK, 2, true, FF, QQ)
+#define FS_LAUNCH_K(KK, FF, QQ) FS_LAUNCH(KK, 1, FF, QQ) FS_LAUNCH(KK, 2, FF, QQ)
   if constexpr (FILL_OK) {
     FS_LAUNCH_K(1, true, false)
     FS_LAUNCH_K(2, true, false)

@@ -2,8 +2,8 @@
 #include "sim_kernel.hpp"
 
 namespace fs {
-hipError_t launch_sim_sjf_prefill(const SimArgs& a, int K, int NW, bool general,
-                                   int waves_per_block, size_t lds_bytes, hipStream_t s) {
-  return launch_sim<POL_SJF, false, true>(a, K, NW, general, waves_per_block, lds_bytes, s);
+hipError_t launch_sim_sjf_prefill(const SimArgs& a, int K, int NW, int waves_per_block,
+                                  size_t lds_bytes, hipStream_t s) {
+  return launch_sim<POL_SJF, false, true>(a, K, NW, waves_per_block, lds_bytes, s);
 }
 }  // namespace fs

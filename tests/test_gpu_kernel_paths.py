@@ -84,3 +84,27 @@ def test_two_worker_tables_beyond_lds(dev):
     # two long jobs run together, so their search ends at once
     T = check_opt(dev, "long", z, z, o, B=2, alpha=130, M_kv=200)
     assert (T[:2] == o[:2].sum(1)).all()
+
+
+@pytest.mark.parametrize("policy,alpha,prefill", [
+    ("fcfs", ALPHA_INF, False), ("sjf", ALPHA_INF, False), ("ljf", 6, False),
+    ("isjl", 40, False), ("isjl", ALPHA_INF, False), ("isjl", 5, True), ("fcfs", ALPHA_INF, True),
+])
+@pytest.mark.parametrize("n,B", [(1, 1), (63, 5), (65, 64), (1025, 130), (2048, 512),
+                                 (2049, 100), (4096, 1000)])
+def test_releases_in_another_order(dev, policy, alpha, prefill, n, B):
+    """Arrivals not sorted by job index, beside sorted instances of the same launch: shuffled,
+    reversed, all equal but one, the last below the largest unsorted arrival (2^20)."""
+    rng = np.random.default_rng(n + B)
+    size = (7, n)
+    a = np.sort(rng.integers(0, 4 * n, size=size), axis=1).astype(np.int32)
+    p = rng.integers(0, 40, size=size).astype(np.int32)
+    o = rng.integers(1, 60, size=size).astype(np.int32)
+    a[1] = rng.permutation(a[1])
+    a[2] = a[2][::-1]
+    a[3] = 0
+    a[3, 0] = 17
+    a[4] = rng.integers(0, 3, size=n)  # many releases at once
+    a[5, 0] = (1 << 20) - 1
+    check(dev, f"{policy} n={n} B={B}", np.ascontiguousarray(a), p, o, prefill=prefill,
+          policy=policy, B=B, alpha=alpha, M_kv=[0, 900][n % 2], cost_c=3, cost_tau=2)
