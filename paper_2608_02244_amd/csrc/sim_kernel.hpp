@@ -442,6 +442,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
   int qcount = 0;         // queued jobs: released, not admitted, not planned
   int chunk = -1;         // release chunk loaded in rel_t / rel_r
   int rel_t = IDLE, rel_r = 0;
+  int rel_nx = IDLE;      // release of the first job after the loaded chunk
   int head = 0;           // FCFS: first waiting rank
   // ISJL
   int mode = 0;           // 0 FILL, 1 DRAIN
@@ -500,6 +501,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       rel_r = RK[j];
       rel_t = A[unsorted ? pid(W[rel_r]) : j];
     }
+    // (not looked up for unsorted arrivals: the chunk's last release step is
+    // taken to go on after it)
+    const int jn = (c + 1) * WAVE;
+    rel_nx = jn >= n ? IDLE : (unsorted ? readlane(rel_t, WAVE - 1) : uni(A[jn]));
     chunk = c;
   };
 
@@ -685,6 +690,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
     }
     gather_first(G);
     return admit_prefix(t, G, need_empty_queue, adm, adm_minlen);
+  };
+
+  // Section 5 sums of the next D steps with the active set as it is (not empty).
+  // The largest footprint grows by one per step, and the span's externality is a
+  // constant: each active job pays the largest footprint minus its own.
+  auto account = [&](int D) {
+    const uint32_t s = (uint32_t)S.nact;
+    const uint32_t m0 = PRE ? (uint32_t)(S.t + S.G + 1) : (uint32_t)(S.t - S.min_s + 1);
+    const uint32_t xe =
+        PRE ? s * (uint32_t)S.G - (S.sp - S.sum_s) : S.sum_s - s * (uint32_t)S.min_s;
+    const int ext = S.max_s - S.min_s;
+    acc.add((uint32_t)D, s, m0, xe, ext, alpha);
+    acc_busy += D;
+    acc_maxext = max(acc_maxext, ext);
+    acc_maxact = max(acc_maxact, S.nact);
   };
 
   // FAIR: launched when every wave of the grid is resident at once, so that the
@@ -1201,6 +1221,119 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       S.max_s = t;
     }
 
+    // Worker 1's planned job waits for its start time.
+    const bool w0_timer = POL == POL_ISJL && planned > 0 && t_w1 > t &&
+                          readlane(ws_end[0], 0) == IDLE &&
+                          ((uint32_t)readlane((int)ws_q[0], 0) & 0xFFFFu) != QNONE;
+
+    // Release sweep (not LJF, which admits at an empty machine only; not with the
+    // prompt prefilled, where the next completion is too close: 16,384 x 2,000
+    // ISJL took 7.44 ms with it, 7.18 without).  With nothing queued and workers idle, every job
+    // is admitted at its release, so a run of releases carries no decision as
+    // long as all of them fit: the jobs of the loaded chunk, in release order,
+    // up to the first one that finds no idle worker, exceeds the KV budget, or
+    // comes at or after a completion (of an active job or of one admitted on
+    // the way), worker 1's start time or the step where A_max passes alpha.  A
+    // release step goes in as a whole or not at all (within one the policy's
+    // order decides who waits).  Planned jobs of idle workers stay blocked
+    // meanwhile: the KV budget only shrinks.  The spans between the release
+    // steps have s = N + i + 1 active jobs after job i, with prefix sums of the
+    // start offsets, and are summed one per lane.
+    //
+    // Event by event each release step costs the scatter into the bitmap, the
+    // gather in priority order, the KV scan and the span sums; while the batch
+    // fills (8 releases per step into 512 workers) those were 67 of 80 events per
+    // instance: 65,536 x 2,000 ISJL at B = 512 5.69 -> 3.72 ms, 4,096 x 1,000 SJF
+    // at B = 64 0.331 -> 0.287 ms.
+    if constexpr (POL != POL_LJF && !PRE) {
+      const int F = POL == POL_ISJL ? free_empty : Beff - S.nact;
+      if ((POL == POL_FCFS ? head == relk : qcount == 0) && relk < n && S.nact > 0 && F > 0 &&
+          (POL != POL_ISJL || mode == 0)) {
+        if ((relk >> 6) != chunk) load_chunk(relk >> 6);
+        const int off = relk & (WAVE - 1);
+        int lim = S.min_end;  // releases before it
+        if (w0_timer) lim = min(lim, t_w1);
+        if (POL == POL_ISJL && alpha < maxlen) lim = min(lim, S.min_s + alpha + 1);
+        if (readlane(rel_t, off) < lim) {
+          const bool in = (lane >= off) & (rel_t < lim);
+          const uint32_t wv = in ? W[rel_r] : 0u;
+          const int id = pid(wv);
+          const int len = in ? true_len(id, plen(wv)) : 0;
+          const int rv = in ? resv_len(id, plen(wv)) : 0;
+          const int end = in ? rel_t + len : IDLE;
+          const int emin = wave_scan_incl_min(end);
+          const int pre = wave_scan_incl(rv);
+          const bool ok = in & (lane - off < F) & (rel_t < emin) & ((M == 0) | (S.res + pre <= M));
+          const uint64_t bad = ballot(!ok & (lane >= off));
+          const int cut = bad ? readlane(rel_t, __builtin_ctzll(bad)) : rel_nx;
+          const int cnt = __builtin_popcountll(ballot(ok & (rel_t < cut)));
+          if (cnt > 0) {
+            const int last = off + cnt - 1;
+            const bool inc = (lane >= off) & (lane <= last);
+            const int t_last = readlane(rel_t, last);
+            const int e_min = min(S.min_end, readlane(emin, last));
+            // the next event: a completion, worker 1's start, or with a worker
+            // left idle the next release
+            int tn = e_min;
+            if (w0_timer) tn = min(tn, t_w1);
+            if (cnt < F) tn = min(tn, last + 1 < WAVE ? readlane(rel_t, last + 1) : rel_nx);
+            const uint32_t xe0 = S.sum_s - (uint32_t)S.nact * (uint32_t)S.min_s;
+            account(readlane(rel_t, off) - t);
+            const int up = dpp<DPP_WAVE_SHL1>(rel_t, rel_t);
+            const int dt = rel_t - S.min_s;
+            const int pdt = wave_scan_incl(inc ? dt : 0);
+            SpanSums here;
+            here.clear();
+            SpanSums& sums = DEFER ? lane_sums : here;
+            if (inc & ((lane == last) | (up > rel_t)))
+              sums.add((uint32_t)((lane == last ? tn : up) - rel_t),
+                       (uint32_t)(S.nact + (lane - off) + 1), (uint32_t)(dt + 1),
+                       xe0 + (uint32_t)pdt, dt, alpha);
+            if constexpr (!DEFER) reduce_lane_sums(here);
+            acc_busy += tn - readlane(rel_t, off);
+            acc_maxext = max(acc_maxext, t_last - S.min_s);
+            acc_maxact = max(acc_maxact, S.nact + cnt);
+            if (inc) emit(id, rel_t, len);
+            int base = 0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+              if (base < cnt) {
+                const bool el = valid[k] & (ws_end[k] == IDLE) &
+                                (POL != POL_ISJL || (ws_q[k] & 0xFFFFu) == QNONE);
+                const uint64_t bm = ballot(el);
+                const int idx = base + mbcnt(bm);
+                const int src = off + min(idx, cnt - 1);
+                const int s2 = __shfl(rel_t, src), e2 = __shfl(end, src);
+                const int r2 = ROB ? __shfl(rv, src) : 0;
+                if (el & (idx < cnt)) {
+                  ws_start[k] = s2;
+                  ws_end[k] = e2;
+                  if (ROB) ws_plan[k] = r2;
+                }
+                base += __builtin_popcountll(bm);
+              }
+            }
+            const uint32_t sdt = (uint32_t)readlane(pdt, last);
+            S.sum_s += (uint32_t)cnt * (uint32_t)S.min_s + sdt;
+            mac(S.sum_start, (uint32_t)cnt, (uint32_t)S.min_s);
+            S.sum_start += sdt;
+            S.res += readlane(pre, last);
+            S.nact += cnt;
+            S.max_s = t_last;
+            S.min_end = e_min;
+            relk += cnt;
+            if (POL == POL_FCFS) head = relk;
+            S.t = tn;
+            if (++iter > iter_max) {
+              failed = true;
+              break;
+            }
+            continue;
+          }
+        }
+      }
+    }
+
     // Fill sweep (up to 2 slots per lane; FCFS, SJF, and ISJL in FILL with
     // nothing planned; jobs queued).  Each coming completion admits the next
     // jobs of the queue's strict prefix that fit the freed slots and the KV
@@ -1615,9 +1748,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
     // The same holds for FCFS, SJF and ISJL in FILL with nothing queued or
     // planned: no completion before the next release carries a decision, so
     // those completions are swept too (when there are a few of them).
-    const bool w0_timer = POL == POL_ISJL && planned > 0 && t_w1 > t &&
-                          readlane(ws_end[0], 0) == IDLE &&
-                          ((uint32_t)readlane((int)ws_q[0], 0) & 0xFFFFu) != QNONE;
     int quiet = 0;  // completions up to the next release, when nothing waits
     if (!PRE && POL != POL_LJF && S.nact > 0 &&
         (POL == POL_FCFS ? head == relk
@@ -1811,14 +1941,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       // span [t, e_0): every job still active; the set only shrinks after it,
       // so it also carries the largest extent and count of the sweep
       {
-        const int ext = S.max_s - S.min_s;
-        acc.add((uint32_t)(e0 - t), (uint32_t)N, (uint32_t)(t - S.min_s + 1),
-                S.sum_s - (uint32_t)N * (uint32_t)S.min_s, ext, alpha);
-        acc_maxext = max(acc_maxext, ext);
-        acc_maxact = max(acc_maxact, N);
+        account(e0 - t);
       }
       if constexpr (!DEFER) reduce_lane_sums(here);
-      acc_busy += tau_end - t;
+      acc_busy += tau_end - e0;
       if (POL == POL_ISJL && amax_sweep && mode == 0) {
         // Phase TWO switches to DRAIN at the first event before tau_end with an
         // idle worker that has nothing planned (from its first completion, or
@@ -1941,20 +2067,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
     }
 
     // (6) account steps t .. tn-1 (Section 5)
-    if (S.nact != 0) {
-      // largest footprint at step t (it grows by one per step of the span) and
-      // the span's externality: each active job pays the largest footprint
-      // minus its own, a constant over the span
-      const uint32_t s = (uint32_t)S.nact;
-      const uint32_t m0 = PRE ? (uint32_t)(t + S.G + 1) : (uint32_t)(t - S.min_s + 1);
-      const uint32_t xe = PRE ? s * (uint32_t)S.G - (S.sp - S.sum_s)
-                              : S.sum_s - s * (uint32_t)S.min_s;
-      const int ext = S.max_s - S.min_s;
-      acc.add((uint32_t)(tn - t), s, m0, xe, ext, alpha);
-      acc_busy += tn - t;
-      acc_maxext = max(acc_maxext, ext);
-      acc_maxact = max(acc_maxact, S.nact);
-    }
+    if (S.nact != 0) account(tn - t);
     S.t = tn;
   }
   if constexpr (DEFER) reduce_lane_sums(lane_sums);

@@ -108,3 +108,24 @@ def test_releases_in_another_order(dev, policy, alpha, prefill, n, B):
     a[5, 0] = (1 << 20) - 1
     check(dev, f"{policy} n={n} B={B}", np.ascontiguousarray(a), p, o, prefill=prefill,
           policy=policy, B=B, alpha=alpha, M_kv=[0, 900][n % 2], cost_c=3, cost_tau=2)
+
+
+@pytest.mark.parametrize("policy,alpha", [("fcfs", ALPHA_INF), ("sjf", ALPHA_INF), ("isjl", 0),
+                                          ("isjl", 7), ("isjl", 45), ("isjl", ALPHA_INF)])
+@pytest.mark.parametrize("n,B,rate", [(64, 64, 8), (65, 40, 3), (129, 128, 64), (300, 130, 9),
+                                      (700, 512, 21), (700, 600, 5)])
+def test_runs_of_releases_into_idle_workers(dev, policy, alpha, n, B, rate):
+    """Releases while workers are idle: release steps that straddle a chunk of 64 jobs, that end
+    in the middle of the free workers or of the KV budget, that meet a completion (of a job
+    admitted just before, too), worker 1's start time or A_max = alpha."""
+    rng = np.random.default_rng(n + B + rate)
+    k = 24
+    gap = (rng.random((k, n)) < 1.0 / rate) * rng.integers(1, 4, size=(k, n))
+    a = np.cumsum(gap, axis=1).astype(np.int32)
+    o = rng.integers(1, 30, size=(k, n)).astype(np.int32)
+    long = rng.random((k, n)) < np.linspace(0.05, 1.0, k)[:, None]
+    p = np.where(long, rng.integers(20, 120, size=(k, n)), 0).astype(np.int32)
+    a[-1] = rng.permutation(a[-1])
+    for M in (0, 25 * B, 60 * B):
+        check(dev, f"{policy} n={n} B={B} rate={rate} M={M}", a, p, o, policy=policy, B=B,
+              alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
