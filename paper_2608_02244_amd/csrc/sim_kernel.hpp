@@ -191,16 +191,16 @@ struct SpanSums {
 // progress): a job runs one step per output token, reserves prompt + output and
 // its footprint in the batch cost is prompt + progress; fairness stays on
 // progress.  The sweeps are off (completions are taken one event at a time).
-// FILL: with the fill sweep (below), for up to 2 slots per lane.
+// FILL: with the fill sweep (below).
 // QH: ISJL with up to 8 slots per lane whose plan-queue links are in HBM
 // scratch (else in LDS).  Every kernel with up to 8 slots per lane but FCFS's
 // is held to 128 VGPRs, so that 4 waves share a SIMD where the LDS allows 16
 // per CU (FCFS's 4- and 8-slot kernels ran slower that way and keep 3).
 template <int POL, int K, int NW, bool ROB, bool PRE, bool FILL, bool QH = false,
           bool FAIR = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <= 2 || (K <= 8 && POL != POL_FCFS) ? 4 : (K <= 8 ? 3 : 1)))) void simulate_kernel(SimArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (K <= 8 && POL != POL_FCFS) ? 4 : (K <= 8 ? 3 : 1)))) void simulate_kernel(SimArgs a) {
   static_assert(!ROB || POL == POL_ISJL, "predicted sizes: ISJL only");
-  static_assert(!FILL || (K <= 2 && !ROB && !PRE && POL != POL_LJF), "fill sweep variants");
+  static_assert(!FILL || (!ROB && !PRE && POL != POL_LJF), "fill sweep variants");
   extern __shared__ uint32_t lds_raw[];
   // With 4 or 8 slots per lane (but FCFS) the wave's index in its block is
   // taken into a scalar register: every row pointer derived from the instance
@@ -1334,341 +1334,219 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
       }
     }
 
-    // Fill sweep (up to 2 slots per lane; FCFS, SJF, and ISJL in FILL with
-    // nothing planned; jobs queued).  Each coming completion admits the next
-    // jobs of the queue's strict prefix that fit the freed slots and the KV
-    // budget.  While no job admitted meanwhile completes, nothing is released
-    // and (ISJL) A_max stays within alpha at each completion, the admissions
-    // follow from counts: after the completions at the sorted positions <= p,
-    // the first
+    // Fill sweep (FCFS, SJF, and ISJL where alpha never binds, with nothing
+    // planned; jobs queued).  Each coming completion admits the next jobs of the
+    // queue's strict prefix that fit the freed slots and the KV budget.  While no
+    // job admitted meanwhile completes and nothing is released, the admissions
+    // follow from counts: the (at most 64) earliest completions are sorted, and
+    // after those at positions <= p the first
     //   A(p) = min(G, free + p + 1, #{j : PQ_j <= M - res + RR_p})
     // queued jobs are in (PQ_j: summed reservations of the queued jobs 0..j in
     // priority order; RR_p: of the completed positions 0..p; A is
     // non-decreasing), and queued job j starts at the completion of the first
     // position with A(p) > j.  The spans are accounted in parallel as in the
-    // drain sweep, with the admitted jobs added to the suffix sums, up to the
-    // first completion, admitted job's completion, release or (ISJL, KV budget
-    // blocking an idle worker) alpha crossing that the counts do not decide;
-    // the event loop takes it from there.  The last group of completions is
-    // always left to the event loop, so every counted event has a job of the
-    // sorted set still active.
+    // drain sweep, with the other active jobs and the admitted ones added to the
+    // suffix sums, up to the first completion or admitted job's completion that
+    // the counts do not decide; the event loop takes it from there.  The last
+    // group of the sorted completions is always left to the event loop, so every
+    // counted event has a job of the sorted set still active.
+    //
+    // One position and one queued job per lane, however many slots a lane has:
+    // an admitted job's completion ends the run after some tens of completions
+    // (about 55 at B = 512 on the heavy-tailed workload), so sorting every active
+    // job would cost more than it covers.  16,384 x 2,000 FCFS at B = 512, where
+    // every completion was an event: 10.2 -> 1.32 ms.
     if constexpr (FILL) {
       const int Qn = POL == POL_FCFS ? relk - head : qcount;
       if (S.nact >= 2 && Qn > 0 && (POL != POL_ISJL || (mode == 0 && planned == 0))) {
-        int H = IDLE;  // next release
+        // completions before X: before the next release, and before the first
+        // queued job could finish after being admitted at the first of them
+        int X = IDLE;
         if (relk < n) {
           if ((relk >> 6) != chunk) load_chunk(relk >> 6);
-          H = readlane(rel_t, relk & (WAVE - 1));
+          X = readlane(rel_t, relk & (WAVE - 1));
         }
-        // taken when a few completions come before the first queued job could
-        // finish after being admitted at the first of them (ISJL: and before
-        // A_max surely exceeds alpha: some job started by max_s stays active)
         const int r0 = POL == POL_FCFS ? head : pool.first();
-        int64_t lim0 = min((int64_t)H, (int64_t)S.min_end + plen(W[r0]));
-        if (POL == POL_ISJL) lim0 = min(lim0, (int64_t)S.max_s + alpha + 1);
-        int ahead = 0;
+        X = min(X, S.min_end + plen(W[r0]));
+        auto ends_before = [&](int x) -> int {
+          int c = 0;
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-          ahead += __builtin_popcountll(ballot((ws_end[k] != IDLE) & ((int64_t)ws_end[k] < lim0)));
-        if (ahead >= 4) {
+          for (int k = 0; k < K; ++k) c += __builtin_popcountll(ballot(ws_end[k] < x));
+          return c;
+        };
+        int N0 = ends_before(X);  // completions sorted
+        if constexpr (K > 1) {
+          if (N0 > WAVE) {  // an earlier X with at most 64 of them
+            int hi = X;
+            X = S.min_end;
+            N0 = 0;
+            for (int i = 0; i < 10 && N0 < 48; ++i) {
+              const int mid = X + ((hi - X) >> 1), c = ends_before(mid);
+              if (c <= WAVE) {
+                X = mid;
+                N0 = c;
+              } else {
+                hi = mid;
+              }
+            }
+          }
+        }
+        if (N0 >= 4) {
           const int N = S.nact;
-          const int Gq = min(Qn, Beff);
-          constexpr int NS = K * WAVE;
-          // queued job j (register j / 64, lane j % 64) and sorted position q
-          // (lane q / K, register q % K); the shuffles run on every lane
-          auto at_job = [&](const int(&v)[K], int j) -> int {
-            if constexpr (K == 1) {
-              return __shfl(v[0], j & (WAVE - 1));
-            } else {
-              const int v0 = __shfl(v[0], j & (WAVE - 1)), v1 = __shfl(v[1], j & (WAVE - 1));
-              return (j >> 6) ? v1 : v0;
-            }
-          };
-          auto at_pos = [&](const int(&v)[K], int q) -> int {
-            if constexpr (K == 1) {
-              return __shfl(v[0], q & (WAVE - 1));
-            } else {
-              const int v0 = __shfl(v[0], (q >> 1) & (WAVE - 1));
-              const int v1 = __shfl(v[1], (q >> 1) & (WAVE - 1));
-              return (q & 1) ? v1 : v0;
-            }
-          };
-          auto at_job_u = [&](const int(&v)[K], int j) -> int {  // j uniform
-            if constexpr (K == 1) {
-              return readlane(v[0], j);
-            } else {
-              const int v0 = readlane(v[0], j & (WAVE - 1)), v1 = readlane(v[1], j & (WAVE - 1));
-              return (j >> 6) ? v1 : v0;
-            }
-          };
-          auto at_pos_u = [&](const int(&v)[K], int q) -> int {  // q uniform
-            if constexpr (K == 1) {
-              return readlane(v[0], q);
-            } else {
-              const int v0 = readlane(v[0], q >> 1), v1 = readlane(v[1], q >> 1);
-              return (q & 1) ? v1 : v0;
-            }
-          };
-          // active jobs sorted by completion: end - t, progress t - start
-          uint32_t dk[K];
-          int dg[K];
+          // completion - t and progress of the jobs that end before X, packed
+          // into the lanes through the gather buffer with 2 or more slots; the
+          // progress range of the others
+          int e0 = IDLE, g0 = 0, rmax = -1, rmin = IDLE;
 #pragma unroll
           for (int k = 0; k < K; ++k) {
-            const bool act = ws_end[k] != IDLE;
-            dk[k] = act ? (uint32_t)(ws_end[k] - t) : 0xFFFFFFFFu;
-            dg[k] = act ? t - ws_start[k] : 0;
+            const bool other = (ws_end[k] >= X) & (ws_end[k] != IDLE);
+            rmax = max(rmax, other ? t - ws_start[k] : -1);
+            rmin = min(rmin, other ? t - ws_start[k] : IDLE);
           }
-          reg_sort_payload<K>(dk, dg, lane);
-          int de[K];  // completion - t of each position (IDLE past N)
-#pragma unroll
-          for (int k = 0; k < K; ++k) de[k] = lane * K + k < N ? (int)dk[k] : IDLE;
-          const int e_up = dpp<DPP_WAVE_SHL1>(de[0], de[0]);  // first position of the next lane
-          // progress sum / max / min of the positions of the lanes above
-          int xs_g, xs_max, xs_min;
-          {
-            int lg = 0, lmx = -1, lmn = IDLE;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-              if (lane * K + k < N) {
-                lg += dg[k];
-                lmx = max(lmx, dg[k]);
-                lmn = min(lmn, dg[k]);
-              }
+          rmax = wave_max(rmax);
+          rmin = wave_min(rmin);
+          if constexpr (K == 1) {
+            if (ws_end[0] < X) {
+              e0 = ws_end[0] - t;
+              g0 = t - ws_start[0];
             }
-            const int incl = wave_scan_incl(lg);
-            xs_g = readlane(incl, WAVE - 1) - incl;
-            const int rmx = wave_scan_incl_max(__shfl(lmx, (WAVE - 1) - lane));
-            const int rmn = wave_scan_incl_min(__shfl(lmn, (WAVE - 1) - lane));
-            const int src = lane < WAVE - 1 ? (WAVE - 2) - lane : 0;
-            xs_max = __shfl(rmx, src);
-            xs_min = __shfl(rmn, src);
-            if (lane == WAVE - 1) {
-              xs_max = -1;
-              xs_min = IDLE;
-            }
-          }
-          // ISJL: completions before the first one after which A_max exceeds
-          // alpha, or (with a KV budget, which may block an idle worker) whose
-          // following span the alpha crossing may cut; fewer than 3 are left
-          // to the event loop
-          bool go = true;
-          if (POL == POL_ISJL) {
-            int lfail = IDLE, lcutq = IDLE;
-            int cg_max = xs_max;
-#pragma unroll
-            for (int k = K - 1; k >= 0; --k) {
-              const int q = lane * K + k;
-              const int e = de[k];
-              const int e_nx = (k + 1 < K) ? de[k + 1 < K ? k + 1 : k] : e_up;
-              if ((q < N) & ((q + 1 >= N) | (e_nx > e))) {
-                if ((q + 1 >= N) | (e + cg_max > alpha)) lfail = q;
-                else if ((M != 0) & (alpha != IDLE) & (alpha + 1 - cg_max < e_nx)) lcutq = q;
-              }
-              if (q < N) cg_max = max(cg_max, dg[k]);
-            }
-            const int qc = wave_min(lcutq);
-            const int qf = min(wave_min(lfail), qc == IDLE ? IDLE : qc + 1);
-            int lbelow = 0;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-              const int q = lane * K + k;
-              const int e_nx = (k + 1 < K) ? de[k + 1 < K ? k + 1 : k] : e_up;
-              if ((q < qf) & (e_nx > de[k])) lbelow++;
-            }
-            go = wave_sum(lbelow) >= 3;
-          }
-          if (go) {
-          if (POL != POL_FCFS) gather_first(Gq);
-          // queued jobs: length and summed reservations in priority order
-          int qlen[K], pq[K];
-          {
-            int carry = 0;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-              const int j = k * WAVE + lane;
-              int L = 0;
-              if (j < Gq) L = plen(W[POL == POL_FCFS ? head + j : (int)STG[j]]);
-              qlen[k] = L;
-              const int inc = wave_scan_incl(L);
-              pq[k] = j < Gq ? carry + inc : IDLE;
-              carry += readlane(inc, WAVE - 1);
-            }
-          }
-          // A(q): queued jobs admitted once the positions <= q have completed
-          int ap[K];
-          {
-            int rr[K], run = 0;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-              if (lane * K + k < N) run += de[k] + dg[k];  // lengths (= reservations)
-              rr[k] = run;
-            }
-            const int rbase = wave_scan_incl(run) - run;
-            const int bud0 = M - S.res;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-              const int q = lane * K + k;
-              int v = min(Gq, Beff - N + q + 1);
-              if (M != 0) {
-                const int64_t b = (int64_t)bud0 + rbase + rr[k];
-                const int bb = b < 0 ? -1 : (b >= (int64_t)IDLE ? IDLE - 1 : (int)b);
-                int lo = 0;  // queued jobs whose summed reservations fit
-#pragma unroll
-                for (int step = NS; step >= 1; step >>= 1) {
-                  const int x = at_job(pq, min(lo + step, NS) - 1);
-                  if ((lo + step <= NS) & (x <= bb)) lo += step;
-                }
-                v = min(v, lo);
-              }
-              ap[k] = q < N ? v : IDLE;
-            }
-          }
-          // start of queued job j relative to t (IDLE: not admitted at these
-          // positions), the earliest completion among jobs 0..j and their
-          // summed starts
-          int sg[K], pm[K], sa[K];
-#pragma unroll
-          for (int k = 0; k < K; ++k) {
-            const int j = k * WAVE + lane;
-            int lo = 0;  // positions with A <= j
-#pragma unroll
-            for (int step = NS; step >= 1; step >>= 1) {
-              const int x = at_pos(ap, min(lo + step, NS) - 1);
-              if ((lo + step <= NS) & (x <= j)) lo += step;
-            }
-            const int e = at_pos(de, min(lo, NS - 1));
-            sg[k] = lo < N ? e : IDLE;
-          }
-          {
-            int cm = IDLE, cs = 0;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-              const int im = wave_scan_incl_min(sg[k] == IDLE ? IDLE : sg[k] + qlen[k]);
-              pm[k] = min(cm, im);
-              cm = min(cm, readlane(im, WAVE - 1));
-              const int is = wave_scan_incl(sg[k] == IDLE ? 0 : sg[k]);
-              sa[k] = cs + is;
-              cs += readlane(is, WAVE - 1);
-            }
-          }
-          const int Hr = H == IDLE ? IDLE : H - t;
-          // Which completions the counts decide: the event at group end q is
-          // taken if nothing is released by then, no admitted job has completed
-          // by then and (ISJL) A_max after it is within alpha; the span after it
-          // ends early (lim) at an admitted job's completion or, with an idle
-          // worker blocked by the KV budget, at the alpha crossing.
-          int lbad = IDLE, lcut = IDLE, lim[K];
-          uint32_t gem = 0u;
-          {
-            int cg_max = xs_max;
-#pragma unroll
-            for (int k = K - 1; k >= 0; --k) {
-              const int q = lane * K + k;
-              const bool vq = q < N;
-              const int e = de[k];
-              const int e_nx = (k + 1 < K) ? de[k + 1 < K ? k + 1 : k] : e_up;
-              const bool ge = vq & ((q + 1 >= N) | (e_nx > e));
-              const int A = vq ? ap[k] : 0;
-              const int pmA = at_job(pm, max(A - 1, 0));
-              lim[k] = IDLE;
-              if (ge) {
-                gem |= 1u << k;
-                bool ok = (q + 1 < N) & (e < Hr) & ((A == 0) | (pmA > e));
-                if (POL == POL_ISJL) ok = ok && e + cg_max <= alpha;
-                if (!ok) {
-                  lbad = q;
-                } else {
-                  int cut = A > 0 ? pmA : IDLE;
-                  if (POL == POL_ISJL && alpha != IDLE && N - 1 - q + A < Beff && A < Qn)
-                    cut = min(cut, alpha + 1 - cg_max);
-                  if (cut < e_nx) lcut = q;
-                  lim[k] = min(min(e_nx, Hr), cut);
-                }
-              }
-              if (vq) cg_max = max(cg_max, dg[k]);
-            }
-          }
-          const int pe = wave_min(lbad), pc = wave_min(lcut);
-          int p_m;
-          {
-            int lpm = -1;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-              const int q = lane * K + k;
-              if (((gem >> k) & 1u) & (q < pe) & (q <= pc)) lpm = q;
-            }
-            p_m = wave_max(lpm);
-          }
-          const int e_first = readlane(de[0], 0);
-          if (POL == POL_ISJL && kv_block && alpha != IDLE && S.min_s + alpha + 1 - t < e_first)
-            p_m = -1;  // the crossing comes first
-          int tau_rel;
-          if (p_m >= 0) {
-            tau_rel = at_pos_u(lim, p_m);
           } else {
-            tau_rel = min(e_first, Hr);
-            if (POL == POL_ISJL && kv_block && alpha != IDLE)
-              tau_rel = min(tau_rel, S.min_s + alpha + 1 - t);
+            int base = 0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+              const bool act = ws_end[k] < X;
+              const uint64_t bm = ballot(act);
+              if (act) PEND[base + mbcnt(bm)] = (uint32_t)(ws_end[k] - t);
+              base += __builtin_popcountll(bm);
+            }
+            wave_lds_sync();
+            if (lane < N0) e0 = (int)PEND[lane];
+            wave_lds_sync();
+            base = 0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+              const bool act = ws_end[k] < X;
+              const uint64_t bm = ballot(act);
+              if (act) PEND[base + mbcnt(bm)] = (uint32_t)(t - ws_start[k]);
+              base += __builtin_popcountll(bm);
+            }
+            wave_lds_sync();
+            if (lane < N0) g0 = (int)PEND[lane];
+            wave_lds_sync();
           }
-          const int A_m = p_m >= 0 ? at_pos_u(ap, p_m) : 0;
-          // spans after each counted event, with the jobs at the positions
-          // above and the admitted jobs 0..A-1
+          // sorted by completion: the lane rides in the low bits of the key
+          // (completion - t is below 2^20)
+          uint32_t key[1] = {e0 != IDLE ? ((uint32_t)e0 << 6) | (uint32_t)lane : 0xFFFFFFFFu};
+          reg_sort_keys<1, true>(key, lane);
+          const bool vq = lane < N0;
+          const int e = vq ? (int)(key[0] >> 6) : IDLE;
+          const int gs = __shfl(g0, (int)(key[0] & 63u));
+          const int g = vq ? gs : 0;
+          const int e_nx = dpp<DPP_WAVE_SHL1>(e, e);  // of the next position (IDLE past N0)
+          // progress of the jobs active after this position but the admitted
+          // ones: those above and the others
+          const int gsum = (int)((uint32_t)N * (uint32_t)t - S.sum_s) - wave_scan_incl(g);
+          int gmax = wave_scan_incl_max(__shfl(vq ? g : -1, (WAVE - 1) - lane));
+          int gmin = wave_scan_incl_min(__shfl(vq ? g : IDLE, (WAVE - 1) - lane));
+          {
+            const int src = lane < WAVE - 1 ? (WAVE - 2) - lane : 0;
+            gmax = __shfl(gmax, src);
+            gmin = __shfl(gmin, src);
+            gmax = max(lane < WAVE - 1 ? gmax : -1, rmax);
+            gmin = min(lane < WAVE - 1 ? gmin : IDLE, rmin);
+          }
+          // queued job per lane: length, and summed reservations in priority order
+          const int Gq = min(Qn, WAVE);
+          if (POL != POL_FCFS) gather_first(Gq);
+          const uint32_t qw =
+              lane < Gq ? W[POL == POL_FCFS ? head + lane : (int)STG[lane]] : 0u;
+          const int qlen = plen(qw);
+          const int qsum_l = wave_scan_incl(qlen);
+          const int pq = lane < Gq ? qsum_l : IDLE;
+          // A: queued jobs admitted once the positions <= this one have completed
+          const int room = Beff - N + lane + 1;
+          int A = min(Gq, room);
+          if (M != 0) {
+            // lengths are the reservations
+            const int b = M - (S.res - wave_scan_incl(vq ? e + g : 0));
+            int lo = 0;  // queued jobs whose summed reservations fit
+#pragma unroll
+            for (int step = WAVE; step >= 1; step >>= 1) {
+              const int x = __shfl(pq, min(lo + step, WAVE) - 1);
+              if ((lo + step <= WAVE) & (x <= b) & (x != IDLE)) lo += step;
+            }
+            A = min(A, lo);
+          }
+          // more jobs than the gathered ones might be admitted
+          const bool more = (Gq < Qn) & (A == Gq) & (room > Gq);
+          const int ap = vq ? A : IDLE;
+          if (!vq) A = 0;
+          // start of queued job `lane` relative to t (IDLE: not admitted at these
+          // positions), the earliest completion among jobs 0..lane and their
+          // summed starts
+          int sg;
+          {
+            int lo = 0;  // positions with A <= lane
+#pragma unroll
+            for (int step = WAVE; step >= 1; step >>= 1) {
+              const int x = __shfl(ap, min(lo + step, WAVE) - 1);
+              if ((lo + step <= WAVE) & (x <= lane)) lo += step;
+            }
+            const int es = __shfl(e, min(lo, WAVE - 1));
+            sg = lo < N0 ? es : IDLE;
+          }
+          const int pm = wave_scan_incl_min(sg == IDLE ? IDLE : sg + qlen);
+          const int sa = wave_scan_incl(sg == IDLE ? 0 : sg);
+          // Which completions the counts decide: the event at group end q is
+          // taken if no admitted job has completed by then; the span after it
+          // ends early at an admitted job's completion.
+          const int pmx = __shfl(pm, max(A - 1, 0)), sax = __shfl(sa, max(A - 1, 0)),
+                    sgx = __shfl(sg, max(A - 1, 0));
+          const int pmA = A > 0 ? pmx : IDLE;
+          const uint64_t ge = ballot(vq & (e_nx > e));
+          const uint64_t open = ge & ballot((lane + 1 >= N0) | (pmA <= e) | more);
+          const uint64_t cut = ge & ~open & ballot(pmA < e_nx);
+          // taken: the group ends below the first open one, up to the first cut one
+          uint64_t taken = ge & (open ? (open & -open) - 1 : ~0ull);
+          if (cut) taken &= (cut & -cut) | ((cut & -cut) - 1);
+          const int p_m = taken ? 63 - __builtin_clzll(taken) : -1;
+          const int e_first = readlane(e, 0);
+          const int tau_rel = p_m >= 0 ? readlane(min(e_nx, pmA), p_m) : e_first;
+          const int A_m = p_m >= 0 ? readlane(A, p_m) : 0;
+          // spans after each counted event, with the jobs still active and the
+          // admitted jobs 0..A-1
           SpanSums here;
           here.clear();
           SpanSums& sums = DEFER ? lane_sums : here;
           int lmx = 0, lma = 0;
-          {
-            int cg = xs_g, cg_max = xs_max, cg_min = xs_min;
-#pragma unroll
-            for (int k = K - 1; k >= 0; --k) {
-              const int q = lane * K + k;
-              const bool vq = q < N;
-              const int e = de[k];
-              const int e_nx = (k + 1 < K) ? de[k + 1 < K ? k + 1 : k] : e_up;
-              const int A = vq ? ap[k] : 0;
-              const int saA = at_job(sa, max(A - 1, 0)), sgA = at_job(sg, max(A - 1, 0));
-              if (((gem >> k) & 1u) & (q <= p_m)) {
-                const int Er = q == p_m ? tau_rel : e_nx;
-                // starts relative to t: -cg_max the earliest, sgA (of the last
-                // admitted job) or -cg_min the latest
-                const int s = N - 1 - q + A;
-                const int ext = (A > 0 ? sgA : -cg_min) + cg_max;
-                sums.add((uint32_t)(Er - e), (uint32_t)s, (uint32_t)(e + cg_max + 1),
-                         (uint32_t)(s * cg_max - cg + (A > 0 ? saA : 0)), ext, alpha);
-                lmx = max(lmx, ext);
-                lma = max(lma, s);
-              }
-              if (vq) {
-                cg += dg[k];
-                cg_max = max(cg_max, dg[k]);
-                cg_min = min(cg_min, dg[k]);
-              }
-            }
+          if ((taken >> lane) & 1u) {
+            // starts relative to t: -gmax the earliest, sgx (of the last
+            // admitted job) or -gmin the latest
+            const int s = N - 1 - lane + A;
+            const int ext = (A > 0 ? sgx : -gmin) + gmax;
+            sums.add((uint32_t)((lane == p_m ? tau_rel : e_nx) - e), (uint32_t)s,
+                     (uint32_t)(e + gmax + 1),
+                     (uint32_t)(s * gmax - gsum + (A > 0 ? sax : 0)), ext, alpha);
+            lmx = ext;
+            lma = s;
           }
-          // span [t, first event): the jobs active now
-          {
-            const int ext = S.max_s - S.min_s;
-            acc.add((uint32_t)(p_m >= 0 ? e_first : tau_rel), (uint32_t)N,
-                    (uint32_t)(t - S.min_s + 1), S.sum_s - (uint32_t)N * (uint32_t)S.min_s, ext,
-                    alpha);
-            lmx = max(lmx, ext);
-            lma = max(lma, N);
-          }
+          account(e_first);  // span [t, first event): the jobs active now
           if constexpr (!DEFER) reduce_lane_sums(here);
-          acc_busy += tau_rel;
+          acc_busy += tau_rel - e_first;
           acc_maxext = max(acc_maxext, wave_max(lmx));
           acc_maxact = max(acc_maxact, wave_max(lma));
           // starts of the admitted jobs
+          const bool adm_l = lane < A_m;
           mac(S.sum_start, (uint32_t)A_m, (uint32_t)t);
-          if (A_m > 0) S.sum_start += (uint32_t)at_job_u(sa, A_m - 1);
+          if (A_m > 0) S.sum_start += (uint32_t)readlane(sa, A_m - 1);
+          if (adm_l) emit(pid(qw), t + sg, qlen);
           // retire every job done by tau, then seat the admitted ones that are
           // still running
           const int tau = t + tau_rel;
-          int lret = 0;
+          S.ndone += ends_before(tau + 1) + __builtin_popcountll(ballot(adm_l & (sg + qlen <= tau_rel)));
 #pragma unroll
           for (int k = 0; k < K; ++k) {
             if (ws_end[k] <= tau) {
-              lret++;
               ws_end[k] = IDLE;
               ws_start[k] = IDLE;
             }
@@ -1677,23 +1555,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
             int base = 0;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-              const bool idle = valid[k] & (ws_end[k] == IDLE);
-              const uint64_t bm = ballot(idle);
-              const int idx = base + mbcnt(bm);
-              const int jc = min(idx, A_m - 1);
-              const int s_rel = at_job(sg, jc), L = at_job(qlen, jc);
-              if (idle & (idx < A_m)) {
-                const int rk = POL == POL_FCFS ? head + idx : (int)STG[idx];
-                const int st = t + s_rel;
-                emit(pid(W[rk]), st, L);
-                if (st + L > tau) {
+              if (base < A_m) {
+                const bool idle = valid[k] & (ws_end[k] == IDLE);
+                const uint64_t bm = ballot(idle);
+                const int idx = base + mbcnt(bm);
+                const int jc = min(idx, A_m - 1);
+                const int st = t + __shfl(sg, jc), en = st + __shfl(qlen, jc);
+                if (idle & (idx < A_m) & (en > tau)) {
                   ws_start[k] = st;
-                  ws_end[k] = st + L;
-                } else {
-                  lret++;
+                  ws_end[k] = en;
                 }
+                base += __builtin_popcountll(bm);
               }
-              base += __builtin_popcountll(bm);
             }
             if (POL == POL_FCFS) {
               head += A_m;
@@ -1702,26 +1575,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
               qcount -= A_m;
             }
           }
-          S.ndone += wave_sum(lret);
           {
             int cnt = 0, lres = 0, mn = IDLE, mx = -1, me = IDLE;
             uint32_t ss = 0;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-              if (ws_end[k] != IDLE) {
-                cnt++;
-                lres += ws_end[k] - ws_start[k];
-                ss += (uint32_t)ws_start[k];
-                mn = min(mn, ws_start[k]);
-                mx = max(mx, ws_start[k]);
-                me = min(me, ws_end[k]);
-              }
+              const bool act = ws_end[k] != IDLE;
+              cnt += __builtin_popcountll(ballot(act));
+              lres += act ? ws_end[k] - ws_start[k] : 0;
+              ss += act ? (uint32_t)ws_start[k] : 0u;
+              mn = min(mn, ws_start[k]);
+              mx = max(mx, act ? ws_start[k] : -1);
+              me = min(me, ws_end[k]);
             }
-            S.nact = wave_sum(cnt);
+            S.nact = cnt;
             S.res = wave_sum(lres);
             S.sum_s = (uint32_t)wave_sum((int)ss);
-            S.min_s = S.nact > 0 ? wave_min(mn) : IDLE;
-            S.max_s = S.nact > 0 ? wave_max(mx) : -1;
+            S.min_s = wave_min(mn);
+            S.max_s = wave_max(mx);
             S.min_end = wave_min(me);
           }
           S.t = tau;
@@ -1730,7 +1601,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FILL || K <
             break;
           }
           continue;
-          }
         }
       }
     }
@@ -2112,17 +1982,17 @@ inline bool resident_at_once(const void* kern, int64_t blocks, int wpb, size_t l
   return blocks <= (int64_t)per_cu * n_cu;
 }
 
-// The fill sweep serves FCFS and SJF with up to 2 slots per lane, and ISJL there
-// when alpha is at least the length limit (A_max, below every length, never
-// exceeds it).  With a finite budget ISJL's completions mostly meet the guard
-// one at a time, and its event loop runs faster without the sweep's code.
+// The fill sweep serves FCFS and SJF, and ISJL when alpha is at least the length
+// limit (A_max, below every length, never exceeds it).  With a finite budget
+// ISJL's completions mostly meet the guard one at a time, and its event loop
+// runs faster without the sweep's code.
 template <int POL, bool ROB = false, bool PRE = false>
 hipError_t launch_sim(const SimArgs& a, int K, int NW, int wpb, size_t lds, hipStream_t s) {
   const int64_t blocks = (a.n_inst + wpb - 1) / wpb;
   dim3 grid((unsigned)blocks), block((unsigned)(wpb * WAVE));
   constexpr bool FILL_OK = !ROB && !PRE && POL != POL_LJF;
   constexpr bool FILL_ALWAYS = FILL_OK && POL != POL_ISJL;
-  const bool fill = FILL_OK && K <= 2 && (FILL_ALWAYS || a.alpha >= (int)LEN_LIMIT);
+  const bool fill = FILL_OK && (FILL_ALWAYS || a.alpha >= (int)LEN_LIMIT);
   // ISJL plan-queue links in HBM scratch (a kernel of its own, up to 8 slots per
   // lane; the fill-sweep kernels run with alpha at least every length, so
   // nothing is planned there)
@@ -2145,10 +2015,16 @@ hipError_t launch_sim(const SimArgs& a, int K, int NW, int wpb, size_t lds, hipS
   if constexpr (FILL_OK) {
     FS_LAUNCH_K(1, true, false)
     FS_LAUNCH_K(2, true, false)
+    FS_LAUNCH_K(4, true, false)
+    FS_LAUNCH_K(8, true, false)
+    FS_LAUNCH_K(16, true, false)
   }
   if constexpr (!FILL_ALWAYS) {
     FS_LAUNCH_K(1, false, false)
     FS_LAUNCH_K(2, false, false)
+    FS_LAUNCH_K(4, false, false)
+    FS_LAUNCH_K(8, false, false)
+    FS_LAUNCH_K(16, false, false)
   }
   if constexpr (POL == POL_ISJL) {
     FS_LAUNCH_K(1, false, true)
@@ -2156,9 +2032,6 @@ hipError_t launch_sim(const SimArgs& a, int K, int NW, int wpb, size_t lds, hipS
     FS_LAUNCH_K(4, false, true)
     FS_LAUNCH_K(8, false, true)
   }
-  FS_LAUNCH_K(4, false, false)
-  FS_LAUNCH_K(8, false, false)
-  FS_LAUNCH_K(16, false, false)
 #undef FS_LAUNCH_K
 #undef FS_LAUNCH
   return hipErrorInvalidValue;

@@ -129,3 +129,27 @@ def test_runs_of_releases_into_idle_workers(dev, policy, alpha, n, B, rate):
     for M in (0, 25 * B, 60 * B):
         check(dev, f"{policy} n={n} B={B} rate={rate} M={M}", a, p, o, policy=policy, B=B,
               alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
+
+
+@pytest.mark.parametrize("policy,alpha", [("fcfs", ALPHA_INF), ("sjf", ALPHA_INF),
+                                          ("isjl", ALPHA_INF), ("isjl", 1 << 20)])
+@pytest.mark.parametrize("n,B", [(90, 2), (200, 64), (260, 65), (500, 200), (900, 300),
+                                 (1500, 600)])
+def test_fill_sweep_over_many_slots(dev, policy, alpha, n, B):
+    """Runs of completions that admit queued jobs, 1 to 16 slots per lane: long runs (every job
+    long), runs cut by short jobs, more than 64 completions at one step, more than 64 jobs
+    admitted by one run (a long job holding the KV budget back first), releases between."""
+    rng = np.random.default_rng(n + B)
+    size = (6, n)
+    a = np.zeros(size, np.int32)
+    a[1] = np.sort(rng.integers(0, 600, size=n))
+    p = np.zeros(size, np.int32)
+    o = rng.integers(100, 260, size=size).astype(np.int32)
+    o[2] = rng.integers(1, 400, size=n)
+    o[3] = 50 * rng.integers(1, 4, size=n)  # completions at few distinct steps
+    o[4] = rng.integers(3, 9, size=n)
+    o[4, ::40] = 5 * B  # jobs that fill most of the budget alone
+    a[5] = rng.permutation(np.arange(n) // 7)
+    for M in (0, 6 * B, 150 * B):
+        check(dev, f"{policy} alpha={alpha} n={n} B={B} M={M}", a, p, o, policy=policy, B=B,
+              alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
