@@ -153,3 +153,28 @@ def test_fill_sweep_over_many_slots(dev, policy, alpha, n, B):
     for M in (0, 6 * B, 150 * B):
         check(dev, f"{policy} alpha={alpha} n={n} B={B} M={M}", a, p, o, policy=policy, B=B,
               alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
+
+
+@pytest.mark.parametrize("alpha", [3, 40, 200])
+@pytest.mark.parametrize("n,B", [(64, 3), (200, 16), (420, 65), (900, 130), (1500, 520),
+                                 (1200, 1000), (2500, 60)])
+def test_pack_scan_batches(dev, n, B, alpha):
+    """Phase ONE's pack scan over batches of 64 candidates: packs that span batches, spare and
+    long workers, candidates that fit nowhere (runs of them, to the next batch and to the end of
+    the queue), no candidate at all; plan links in LDS and in HBM."""
+    rng = np.random.default_rng(n + B + alpha)
+    size = (8, n)
+    z = np.zeros(size, np.int32)
+    short = rng.integers(1, max(2, alpha // 6 + 1), size=size)
+    mid = rng.integers(max(1, alpha // 2), alpha + 1, size=size)
+    long = rng.integers(alpha + 1, 5 * alpha + 9, size=size)
+    u = rng.random(size)
+    share = np.linspace(0.0, 0.9, 8)[:, None]  # of short jobs
+    o = np.where(u < share, short, np.where(u < share + 0.05, mid, long)).astype(np.int32)
+    o[1, : n - 2] = 1 + np.arange(n - 2) % max(1, alpha)  # two long jobs, the rest pack
+    o[1, n - 2:] = 4 * alpha + 1
+    a = z.copy()
+    a[2:5] = np.sort(rng.integers(0, 9 * alpha, size=(3, n)), axis=1)
+    for M in (0, 2 * B * alpha):
+        check(dev, f"n={n} B={B} alpha={alpha} M={M}", a, z, o, policy="isjl", B=B, alpha=alpha,
+              M_kv=M, cost_c=3, cost_tau=2)
