@@ -1,16 +1,23 @@
 // Re-scoring of given schedules (Section 5, profit decomposition; eq. (1) checks):
-// one wavefront per instance.
+// one wavefront per instance, two beyond 512 jobs.
 //
-// The 2n start/end events are sorted (in registers, or in LDS beyond 4,096
-// events) as packed keys
+// The 2n start/end events are sorted in registers as packed keys
 //   time << 13 | kind << 12 | index      (kind 0 = end, 1 = start)
 // so that at equal times completions come before starts, matching the step
 // model (a job ending at t frees its slot for a job starting at t).  Between
 // two event times the active set is fixed and the Section 5 terms are summed
 // in closed form, as in the simulation kernel; the sweep itself is described
 // where it runs.
-#include <type_traits>
-
+//
+// The sweep is a chain of dependent steps of 64 events, and the sorted events
+// and job lengths (20 KB at 2,000 jobs) let 8 instances share a CU's LDS: with
+// one wave each, two waves per SIMD, the chain's latency was exposed (VALU busy
+// half of the time).  Two waves per instance share its events: each sorts half
+// of them (32 keys per lane, which brings the kernel under 128 VGPRs), one
+// exchange through LDS and a half-clean merge the halves, and each sweeps its
+// half of the sorted events from a state counted from the events before it.
+// 65,536 x 2,000: 3.73 -> 3.02 ms (2.80 with the counts from lane masks, the
+// doubled sums and the short way through large groups).
 #include "dec_common.hpp"
 #include "regsort.hpp"
 #include "wave.hpp"
@@ -21,27 +28,24 @@ namespace {
 
 constexpr int IDLE32 = 0x7FFFFFFF;
 
-__device__ inline void dec_sort(uint32_t* W, int NP, int lane) {
-  for (int k = 2; k <= NP; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = lane; i < (NP >> 1); i += WAVE) {
-        int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-        int hi = lo + j;
-        bool up = (lo & k) == 0;
-        uint32_t x = W[lo], y = W[hi];
-        if ((x > y) == up) {
-          W[lo] = y;
-          W[hi] = x;
-        }
-      }
-      wave_lds_sync();
-    }
-  }
-}
+// Totals of the job table that both waves of an instance need.
+struct DecShared {
+  uint32_t flags, maxlen, tmax, pad;
+  unsigned long long osum;
+};
+
+// One wave's sums.
+struct DecSums {
+  uint64_t E, X, SM, SSM, q2;
+  int64_t csum, asum;
+  uint32_t D, B, U, P;
+  int Xm, Am;
+  uint32_t v;
+};
 
 __device__ inline void dec_marker(fsched_metrics* out, uint32_t* viol, int64_t inst, int64_t code,
-                                  uint32_t v, int lane) {
-  if (lane == 0) {
+                                  uint32_t v, bool writer) {
+  if (writer) {
     fsched_metrics m;
     m.T = code;
     m.O = m.Q = m.E = m.C = m.W = 0;
@@ -55,144 +59,173 @@ __device__ inline void dec_marker(fsched_metrics* out, uint32_t* viol, int64_t i
 
 }  // namespace
 
-// NARROW: lengths are kept as 16-bit values (an instance with a job of 65,536
-// tokens or more is left to the wide pass).
-template <bool NARROW>
-__global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
+// NP2: events, rounded up to a power of two; G: waves per instance (a block of
+// its own when there are two).
+constexpr int dec_waves(int NP2) { return NP2 > 1024 ? 2 : 1; }
+
+template <int NP2, int G>
+__global__ __launch_bounds__(G == 1 ? 256 : WAVE * G)
+__attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(DecArgs a) {
   extern __shared__ uint32_t lds_raw[];
   const int wib = threadIdx.x >> 6;
-  const int64_t inst = (int64_t)blockIdx.x * (blockDim.x >> 6) + wib;
+  const int g = G == 1 ? 0 : uni(wib);  // this wave's share of the instance
+  const int64_t inst = G == 1 ? (int64_t)blockIdx.x * (blockDim.x >> 6) + wib : (int64_t)blockIdx.x;
   if (inst >= a.n_inst) return;
   const int lane = lane_id();
   const int n = a.n;
-  uint32_t* EV = lds_raw + (size_t)wib * (size_t)a.wave_words;
-  using len_t = typename std::conditional<NARROW, uint16_t, int32_t>::type;
-  len_t* LEN = (len_t*)(EV + a.NP2);  // per job: prompt + output
-  if (!NARROW && a.deferred_only && a.out[inst].T != DEC_DEFERRED) return;
+  uint32_t* EV = lds_raw + (G == 1 ? (size_t)wib * (size_t)a.wave_words : 0);
+  uint16_t* LEN = (uint16_t*)(EV + NP2);  // per job: prompt + output
+  DecShared* SH = (DecShared*)(EV + a.wave_words) - 1;
   const int64_t row = inst * (int64_t)n;
   const int32_t* A = a.arrival + row;
   const int32_t* P = a.prompt + row;
   const int32_t* O = a.output + row;
   const int32_t* S0 = a.start + row;
+  auto sync = [&]() {
+    if constexpr (G == 1) wave_lds_sync();
+    else __syncthreads();
+  };
 
   // One pass over the job table: validation, instance totals, the two event
   // keys of every job (end: (s + len, 0, i), start: (s, 1, i); they are only
   // sorted once the table is known to be valid) and the lengths.  The rows are
   // software-pipelined: the loads of row r + PF are issued while row r is
-  // processed (clamped indices keep every load in bounds).
-  const int NE = 2 * n, NP2 = a.NP2;
-  int bad = 0, neg = 0, early = 0, big = 0, maxlen = 0;
-  int64_t osum = 0, qsum = 0, csum = 0, lsum = 0, tmax = 0;
+  // processed (clamped indices keep every load in bounds).  Every sum but the
+  // arrivals' fits 32 bits per lane in an instance that is scored (at most 64
+  // rows, lengths < 2^20, completions < 2^19).
+  const int NE = 2 * n;
+  if (G > 1) {
+    if (threadIdx.x == 0) SH->flags = SH->maxlen = SH->tmax = SH->osum = 0;
+    __syncthreads();
+  }
+  uint32_t bad = 0, neg = 0, early = 0, big = 0, maxlen = 0, tmax = 0;
+  uint32_t osum32 = 0, csum32 = 0;
+  uint64_t q2 = 0;
+  int64_t asum = 0;
   constexpr int PF = 4;
   int pf_a[PF], pf_p[PF], pf_o[PF], pf_s[PF];
 #pragma unroll
   for (int d = 0; d < PF; ++d) {
-    const int ic = min(d * WAVE + lane, n - 1);
+    const int ic = min((d * G + g) * WAVE + lane, n - 1);
     pf_a[d] = A[ic];
     pf_p[d] = P[ic];
     pf_o[d] = O[ic];
     pf_s[d] = S0[ic];
   }
-  for (int r0 = 0; r0 < n; r0 += PF * WAVE) {
+  for (int r0 = g * WAVE; r0 < n; r0 += PF * G * WAVE) {
 #pragma unroll
     for (int d = 0; d < PF; ++d) {
-      const int i0 = r0 + d * WAVE;
+      const int i0 = r0 + d * G * WAVE;
       if (i0 >= n) break;
       const int i = i0 + lane;
       const int ar = pf_a[d], p = pf_p[d], o = pf_o[d], s = pf_s[d];
       {
-        const int ic = min(i + PF * WAVE, n - 1);
+        const int ic = min(i + PF * G * WAVE, n - 1);
         pf_a[d] = A[ic];
         pf_p[d] = P[ic];
         pf_o[d] = O[ic];
         pf_s[d] = S0[ic];
       }
       if (i < n) {
-        bad |= (ar < 0) | (p < 0) | (o < 1);
-        int64_t len = (int64_t)p + (int64_t)o;
-        big |= (len >= (1 << 20));
-        neg |= (s < 0);
-        early |= (s < ar);
-        int64_t e = (int64_t)s + len;
-        if (e > tmax) tmax = e;
-        if (len < (1 << 20) && len > maxlen) maxlen = (int)len;
-        osum += len;
-        qsum += len * (len + 1) / 2;
-        csum += e;
-        lsum += e - ar;
-        EV[2 * i] = ((uint32_t)(s + p + o) << 13) | (uint32_t)i;
+        bad |= (uint32_t)((ar < 0) | (p < 0) | (o < 1));
+        const uint32_t len = (uint32_t)p + (uint32_t)o;  // below 2^32 in a valid table
+        big |= (uint32_t)(len >= (1u << 20));
+        neg |= (uint32_t)(s < 0);
+        early |= (uint32_t)(s < ar);
+        const uint32_t e = (uint32_t)s + len;
+        tmax = max(tmax, e);
+        maxlen = max(maxlen, len);
+        osum32 += len;
+        q2 += (uint64_t)len * (len + 1u);
+        csum32 += e;
+        asum += ar;
+        EV[2 * i] = (e << 13) | (uint32_t)i;
         EV[2 * i + 1] = ((uint32_t)s << 13) | (1u << 12) | (uint32_t)i;
-        LEN[i] = (len_t)(p + o);
+        LEN[i] = (uint16_t)len;
       }
     }
   }
-  for (int e = NE + lane; e < NP2; e += WAVE) EV[e] = 0xFFFFFFFFu;
-  bad = ballot(bad != 0) != 0;
-  neg = ballot(neg != 0) != 0;
-  early = ballot(early != 0) != 0;
-  big = ballot(big != 0) != 0;
-  if (bad) {
-    dec_marker(a.out, a.viol, inst, FSCHED_T_INVALID, 0u, lane);
-    return;
-  }
-  if (neg) {
-    // a negative start: nothing else is evaluated (bit 16, plus bit 1)
+  for (int e = NE + (int)threadIdx.x % (WAVE * G); e < NP2; e += WAVE * G) EV[e] = 0xFFFFFFFFu;
+  // completions at or beyond 2^31 (not scored) as the largest signed value
+  const uint32_t tcap = min(tmax, 0x7FFFFFFFu), lcap = min(maxlen, 0x7FFFFFFFu);
+  uint32_t flags = (ballot(bad != 0) ? 1u : 0u) | (ballot(neg != 0) ? 2u : 0u) |
+                   (ballot(early != 0) ? 4u : 0u) | (ballot(big != 0) ? 8u : 0u);
+  int maxl = wave_max((int)lcap), tm = wave_max((int)tcap);
+  int64_t osum = wave_sum64((int64_t)osum32);
+  if constexpr (G > 1) {
     if (lane == 0) {
-      fsched_metrics m;
-      m.T = m.O = m.Q = m.E = m.C = m.W = 0;
-      m.sum_completion = m.sum_latency = m.sum_extent = m.busy_steps = 0;
-      m.peak_kv = m.unfair_steps = 0;
-      m.max_extent = m.max_active = 0;
-      a.out[inst] = m;
-      a.viol[inst] = 16u | 1u;
+      atomicOr(&SH->flags, flags);
+      atomicMax(&SH->maxlen, (uint32_t)maxl);
+      atomicMax(&SH->tmax, (uint32_t)tm);
+      atomicAdd(&SH->osum, (unsigned long long)osum);
     }
+    __syncthreads();
+    flags = uniu(SH->flags);
+    maxl = uni((int)SH->maxlen);
+    tm = uni((int)SH->tmax);
+    osum = uni64((int64_t)SH->osum);
+  }
+  const bool writer = lane == 0 && g == 0;
+  if (flags & 1u) {
+    dec_marker(a.out, a.viol, inst, FSCHED_T_INVALID, 0u, writer);
     return;
   }
-  if (big) {
-    dec_marker(a.out, a.viol, inst, FSCHED_T_TOOLARGE, 0u, lane);
+  if (flags & 2u) {  // a negative start: nothing else is evaluated (bit 16, plus bit 1)
+    dec_marker(a.out, a.viol, inst, 0, 16u | 1u, writer);
     return;
   }
-  // tmax via two 32-bit reductions (all ends are >= 0 here)
-  {
-    int hi = wave_max((int)(tmax >> 31));
-    int lo = wave_max((int)(((tmax >> 31) == hi) ? (tmax & 0x7FFFFFFF) : 0));
-    tmax = ((int64_t)hi << 31) | lo;
-  }
-  maxlen = wave_max(maxlen);
-  if (NARROW && maxlen >= 65536) {
-    dec_marker(a.out, a.viol, inst, DEC_DEFERRED, 0u, lane);
-    return;
-  }
-  osum = wave_sum64(osum);
-  qsum = wave_sum64(qsum);
-  csum = wave_sum64(csum);
-  lsum = wave_sum64(lsum);
-  if (tmax >= DEC_TIME_LIMIT) {
-    dec_marker(a.out, a.viol, inst, FSCHED_T_TOOLARGE, 0u, lane);
+  if ((flags & 8u) || (int64_t)tm >= DEC_TIME_LIMIT) {
+    dec_marker(a.out, a.viol, inst, FSCHED_T_TOOLARGE, 0u, writer);
     return;
   }
   {
-    double cb = (double)a.c * (double)tmax + (double)a.tau * (double)osum * (double)maxlen;
-    double wb = (double)a.c * (double)tmax + (double)a.tau * (double)tmax * (double)maxlen;
+    double cb = (double)a.c * (double)tm + (double)a.tau * (double)osum * (double)maxl;
+    double wb = (double)a.c * (double)tm + (double)a.tau * (double)tm * (double)maxl;
     if (cb > 4.0e18 || wb > 4.0e18) {
-      dec_marker(a.out, a.viol, inst, FSCHED_T_RANGE, 0u, lane);
+      dec_marker(a.out, a.viol, inst, FSCHED_T_RANGE, 0u, writer);
       return;
     }
   }
+  // a length of 65,536 tokens or more does not fit the 16-bit table: the
+  // instance reads its lengths from the job table
+  const bool wide = maxl >= 65536;
+  auto len_of = [&](uint32_t key) -> int {
+    const int i = (int)(key & 0xFFFu);
+    return wide ? P[i] + O[i] : (int)LEN[i];
+  };
 
   // ---- events (keys written above) ---------------------------------------------
-  wave_lds_sync();
-  switch (NP2) {  // register sort up to 64 keys per lane, LDS network beyond
-    case 64: wave_reg_sort<1, true>(EV, lane); break;
-    case 128: wave_reg_sort<2, true>(EV, lane); break;
-    case 256: wave_reg_sort<4, true>(EV, lane); break;
-    case 512: wave_reg_sort<8, true>(EV, lane); break;
-    case 1024: wave_reg_sort<16, true>(EV, lane); break;
-    case 2048: wave_reg_sort<32, true>(EV, lane); break;
-    case 4096: wave_reg_sort<64, true>(EV, lane); break;
-    default: dec_sort(EV, NP2, lane); break;
+  sync();
+  {
+    constexpr int KS = NP2 / (WAVE * G);  // keys per lane
+    uint32_t key[KS];
+    uint32_t* mine = EV + g * (KS * WAVE);
+#pragma unroll
+    for (int k = 0; k < KS; ++k) key[k] = mine[k * WAVE + lane];
+    reg_sort_keys<KS, true>(key, lane);
+    if constexpr (G == 2) {
+      // merge the halves: position p against its mirror NP2 - 1 - p in the other
+      // half, the first half keeping the smaller keys, then half-cleaners inside
+      // each half.  The halves pass through LDS one row per register.
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < KS; ++k) mine[k * WAVE + lane] = key[k];
+      __syncthreads();
+      const uint32_t* other = EV + (1 - g) * (KS * WAVE);
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const uint32_t x = other[(KS - 1 - k) * WAVE + (WAVE - 1) - lane];
+        key[k] = g == 0 ? min(key[k], x) : max(key[k], x);
+      }
+      reg_sort_halves<KS, true, KS * WAVE / 2>(key, lane);
+      __syncthreads();
+    } else {
+      wave_lds_sync();
+    }
+#pragma unroll
+    for (int k = 0; k < KS; ++k) mine[lane * KS + k] = key[k];
   }
-  wave_lds_sync();
+  sync();
 
   // ---- sweep ----------------------------------------------------------------
   // 64 sorted events at a time: |S|, the start sum and the reservation sum
@@ -211,7 +244,7 @@ __global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
   const int alpha = a.alpha;
   const int64_t M = a.M;
   const int Bcap = a.B;
-  uint32_t v = early ? 1u : 0u;
+  uint32_t v = (flags & 4u) ? 1u : 0u;
   int c_cnt = 0;                       // |S| before the chunk
   // start sum and reservation sum before the chunk: below 4,096 x 2^19, so
   // they (and every partial sum) are exact in 32 bits
@@ -221,14 +254,14 @@ __global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
   int pmin = 0, pmax = -1;             // first / last of their start events
   int cnt_last = 0;                    // |S| at the last group end
   int g_nst = 0, gfirst = -1, glast = -1;  // starts of the open group (before this chunk)
-  // per lane: E, extent and the two parts of the largest-footprint sums (C and
-  // W take c and tau once at the end) in 64 bits; span lengths, busy and
+  // per lane: E, extent and the doubled largest-footprint sums (C and W take c
+  // and tau once at the end) in 64 bits; span lengths, busy and
   // unfair steps (the spans of one lane are disjoint, so each sum stays below
   // 2^19) and peak KV in 32 bits; extent and |S| maxima
-  uint64_t lE = 0, lX = 0, lSMa = 0, lSMb = 0, lSSMa = 0, lSSMb = 0;
+  uint64_t lE = 0, lX = 0, lSM2 = 0, lSSM2 = 0;
   uint32_t lD = 0, lB = 0, lU = 0, lP = 0;
   int lXm = 0, lAm = 0;
-  bool lcap = false, lkv = false, lunf = false;
+  bool over = false, lkv = false, lunf = false;
   // idle steps before the first event
   const int t_first = (int)(EV[0] >> 13);
   const int64_t c0 = a.c * (int64_t)t_first;
@@ -269,11 +302,10 @@ __global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
         const uint32_t m0 = (uint32_t)(t - gmin + 1);
         const uint32_t sD = s * D;
         // per step of the span the largest footprint is m0, m0 + 1, ...: its sum
-        // is D m0 + D (D - 1) / 2; the halves are taken once at the end
-        lSMa += (uint64_t)D * m0;
-        lSMb += (uint64_t)D * (D - 1u);
-        lSSMa += (uint64_t)sD * m0;
-        lSSMb += (uint64_t)sD * (D - 1u);
+        // is D m0 + D (D - 1) / 2, kept doubled
+        const uint32_t m2 = 2u * m0 + D - 1u;
+        lSM2 += (uint64_t)D * m2;
+        lSSM2 += (uint64_t)sD * m2;
         // sum of (start - earliest start) over the active jobs: < 4,096 x 2^19
         lE += (uint64_t)D * (sum_p - s * (uint32_t)gmin);
         const int ext = gmax - gmin;
@@ -286,7 +318,7 @@ __global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
         lXm = max(lXm, ext);
         lAm = max(lAm, cnt_p);
         lP = max(lP, s * (uint32_t)t_next - sum_p);
-        if ((Bcap > 0) & (cnt_p > Bcap)) lcap = true;
+        if ((Bcap > 0) & (cnt_p > Bcap)) over = true;
         if ((M != 0) & (cnt_p >= 2) & ((int64_t)res_p > M)) lkv = true;
       }
     }
@@ -295,13 +327,59 @@ __global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
   bool q_on = false;
   int q_t = 0, q_tn = 0, q_cnt = 0, q_gmin = 0, q_gmax = 0;
   uint32_t q_sum = 0, q_res = 0;
+  // This wave's events [p0, p1): with two waves, up to and from the first group
+  // that begins in the second half.
+  int p0 = 0, p1 = NE;
+  if constexpr (G == 2) {
+    int bnd = NE;
+    for (int q = n; q < NE; q += WAVE) {
+      const int e = q + lane;
+      const uint64_t m = ballot(e < NE && (EV[e] >> 13) != (EV[e - 1] >> 13));
+      if (m) {
+        bnd = q + __builtin_ctzll(m);
+        break;
+      }
+    }
+    if (g == 0) {
+      p1 = bnd;
+    } else {
+      p0 = bnd;
+      if (bnd < NE) {
+        // the state before it: a job started earlier is active when it ends at
+        // that time or later; nmin = nmax = 0 has the first group end search the
+        // earliest and latest start, from the first and last such start event
+        const int tb = (int)(uniu(EV[bnd]) >> 13);
+        int cnt = 0, first = IDLE32, last = -1;
+        uint32_t ss = 0, sr = 0;
+        for (int e = lane; e < bnd; e += WAVE) {
+          const uint32_t key = EV[e];
+          const int len = len_of(key), t = (int)(key >> 13);
+          const bool on = ((key >> 12) & 1u) & (uint32_t)(t + len >= tb);
+          cnt += on ? 1 : 0;
+          ss += on ? (uint32_t)t : 0u;
+          sr += on ? (uint32_t)len : 0u;
+          first = min(first, on ? e : IDLE32);
+          last = max(last, on ? e : -1);
+        }
+        c_cnt = cnt_last = wave_sum(cnt);
+        c_sum = (uint32_t)wave_sum((int)ss);
+        c_res = (uint32_t)wave_sum((int)sr);
+        if (c_cnt > 0) {
+          pmin = wave_min(first);
+          pmax = wave_max(last);
+          min_s = (int)(uniu(EV[pmin]) >> 13);
+          max_s = (int)(uniu(EV[pmax]) >> 13);
+        }
+      }
+    }
+  }
   // keys and lengths are loaded one chunk ahead
-  uint32_t nkey = lane < NE ? EV[lane] : 0xFFFFFFFFu;
-  int nlen = lane < NE ? (int)LEN[nkey & 0xFFFu] : 0;
+  uint32_t nkey = p0 + lane < NE ? EV[p0 + lane] : 0xFFFFFFFFu;
+  int nlen = p0 + lane < NE ? len_of(nkey) : 0;
 
-  for (int base = 0; base < NE; base += WAVE) {
+  for (int base = p0; base < p1; base += WAVE) {
     const int p = base + lane;
-    const bool valid = p < NE;
+    const bool valid = p < p1;
     const uint32_t key = nkey;
     const int len = nlen;
     const int pn = p + WAVE;
@@ -310,13 +388,11 @@ __global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
     const bool is_start = valid & (((key >> 12) & 1u) != 0u);
     const bool is_end = valid & (((key >> 12) & 1u) == 0u);
     const int sj = is_start ? t : t - len;  // the job's start
-    const int cnt_p = c_cnt + wave_scan_incl(is_start ? 1 : (is_end ? -1 : 0));
     // within a chunk the deltas sum to less than 64 x 2^20 in magnitude (times
-    // < 2^19, lengths < 2^20): 32-bit scans on top of the 64-bit carries
-    const uint32_t sum_p = c_sum + (uint32_t)wave_scan_incl(is_start ? sj : (is_end ? -sj : 0));
-    const uint32_t res_p = c_res + (uint32_t)wave_scan_incl(is_start ? len : (is_end ? -len : 0));
-    span_terms(q_on, q_t, q_tn, q_cnt, q_sum, q_res, q_gmin, q_gmax);
-    nlen = pn < NE ? (int)LEN[nkey & 0xFFFu] : 0;
+    // < 2^19, lengths < 2^20)
+    const int dsum = is_start ? sj : (is_end ? -sj : 0);
+    const int dres = is_start ? len : (is_end ? -len : 0);
+    nlen = pn < NE ? len_of(nkey) : 0;
     // the next event's time: the lane above, and for the last lane the first
     // key of the next chunk
     int t_next = dpp<DPP_WAVE_SHL1, 0xf, 0xf, false>(t, t);
@@ -325,13 +401,34 @@ __global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
     const bool last = p == NE - 1;
     const bool gend = valid & (last | (t_next > t));
     // lane masks, each from one comparison (combined on the scalar unit)
-    const int nv = NE - base;  // valid lanes: 0 .. nv - 1
+    const int nv = p1 - base;  // valid lanes: 0 .. nv - 1
     const uint64_t vmask = nv >= WAVE ? ~0ull : ((1ull << nv) - 1);
     const uint64_t smask = vmask & ballot((key & 0x1000u) != 0u);
     const uint64_t emask = vmask & ~smask;
-    const uint64_t gmask = vmask & (ballot(t_next > t) | (nv <= WAVE ? 1ull << (nv - 1) : 0ull));
+    const uint64_t gmask = vmask & (ballot(t_next > t) | ((nv <= WAVE) & (p1 == NE) ? 1ull << (nv - 1) : 0ull));
     uint64_t emin = emask & ballot(sj == min_s);
     uint64_t emax = emask & ballot(sj == max_s);
+    span_terms(q_on, q_t, q_tn, q_cnt, q_sum, q_res, q_gmin, q_gmax);
+    if (gmask == 0) {
+      // the middle of a large group (a batch that starts or ends together: 4 in
+      // 10 chunks of the schedules of 512 workers): only the state before the
+      // next chunk changes
+      q_on = false;
+      nmin -= __builtin_popcountll(emin);
+      nmax -= __builtin_popcountll(emax);
+      if (smask) {
+        if (g_nst == 0) gfirst = base + __builtin_ctzll(smask);
+        g_nst += __builtin_popcountll(smask);
+        glast = base + 63 - __builtin_clzll(smask);
+      }
+      c_cnt += __builtin_popcountll(smask) - __builtin_popcountll(emask);
+      c_sum += (uint32_t)wave_sum(dsum);
+      c_res += (uint32_t)wave_sum(dres);
+      continue;
+    }
+    const int cnt_p = c_cnt + mbcnt(smask) - mbcnt(emask) + (is_start ? 1 : (is_end ? -1 : 0));
+    const uint32_t sum_p = c_sum + (uint32_t)wave_scan_incl(dsum);
+    const uint32_t res_p = c_res + (uint32_t)wave_scan_incl(dres);
     // Common case, with no walk: the active set is never empty at a group end,
     // the earliest start keeps a job through the chunk, and the latest start
     // can only rise: it keeps a job until the chunk's first start (or a group
@@ -445,7 +542,7 @@ __global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
               if (ee >= 0 && ee <= gpos) {
                 const uint32_t kk = EV[ee];
                 st_time = (int)(kk >> 13);
-                ok = ((kk >> 12) & 1u) && st_time + LEN[kk & 0xFFFu] > tg;
+                ok = ((kk >> 12) & 1u) && st_time + len_of(kk) > tg;
               }
               if (found < 0) {
                 const uint64_t hm = ballot(ok);
@@ -475,7 +572,7 @@ __global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
               if (ee >= 0) {
                 const uint32_t kk = EV[ee];
                 st_time = (int)(kk >> 13);
-                ok = ((kk >> 12) & 1u) && st_time + LEN[kk & 0xFFFu] > tg;
+                ok = ((kk >> 12) & 1u) && st_time + len_of(kk) > tg;
               }
               if (found < 0) {
                 const uint64_t hm = ballot(ok);
@@ -548,51 +645,96 @@ __global__ __launch_bounds__(256) void decompose_kernel(DecArgs a) {
     c_res = (uint32_t)readlane((int)res_p, 63);
   }
   span_terms(q_on, q_t, q_tn, q_cnt, q_sum, q_res, q_gmin, q_gmax);
-  const int64_t acc_E = wave_sum64((int64_t)lE);
-  const int64_t sD = wave_sum((int)lD);  // the busy and idle steps after the first event
-  const int64_t SSM = wave_sum64((int64_t)lSSMa) + wave_sum64((int64_t)lSSMb) / 2;
-  const int64_t SM = wave_sum64((int64_t)lSMa) + wave_sum64((int64_t)lSMb) / 2;
-  const int64_t acc_C = c0 + a.c * sD + a.tau * SSM;
-  const int64_t acc_W = c0 + a.c * sD + a.tau * SM;
-  const int64_t acc_ext = wave_sum64((int64_t)lX);
-  const int64_t acc_busy = wave_sum((int)lB);
-  const int64_t acc_unf = wave_sum((int)lU);
-  const int64_t acc_peak = wave_max((int)lP);  // below 4,096 x 2^19
-  const int acc_maxext = wave_max(lXm);
-  const int acc_maxact = wave_max(lAm);
+  DecSums r;
+  r.E = (uint64_t)wave_sum64((int64_t)lE);
+  r.X = (uint64_t)wave_sum64((int64_t)lX);
+  r.SM = (uint64_t)wave_sum64((int64_t)lSM2) >> 1;  // every term is even
+  r.SSM = (uint64_t)wave_sum64((int64_t)lSSM2) >> 1;
+  r.q2 = (uint64_t)wave_sum64((int64_t)q2);
+  r.csum = wave_sum64((int64_t)csum32);
+  r.asum = wave_sum64(asum);
+  r.D = (uint32_t)wave_sum((int)lD);  // the busy and idle steps after the first event
+  r.B = (uint32_t)wave_sum((int)lB);
+  r.U = (uint32_t)wave_sum((int)lU);
+  r.P = (uint32_t)wave_max((int)lP);  // below 4,096 x 2^19
+  r.Xm = wave_max(lXm);
+  r.Am = wave_max(lAm);
   if (ballot(lunf)) v |= 8u;
-  if (ballot(lcap)) v |= 2u;
+  if (ballot(over)) v |= 2u;
   if (ballot(lkv)) v |= 4u;
+  r.v = v;
+  if constexpr (G == 2) {
+    // the sorted events are no longer read once both waves are here
+    __syncthreads();
+    DecSums* part = (DecSums*)EV;
+    if (g == 1 && lane == 0) *part = r;
+    __syncthreads();
+    if (g == 1) return;
+    const DecSums o = *part;
+    r.E += o.E;
+    r.X += o.X;
+    r.SM += o.SM;
+    r.SSM += o.SSM;
+    r.q2 += o.q2;
+    r.csum += o.csum;
+    r.asum += o.asum;
+    r.D += o.D;
+    r.B += o.B;
+    r.U += o.U;
+    r.P = max(r.P, o.P);
+    r.Xm = max(r.Xm, o.Xm);
+    r.Am = max(r.Am, o.Am);
+    r.v |= o.v;
+  }
 
   if (lane == 0) {
     fsched_metrics m;
-    m.T = tmax;
+    m.T = tm;
     m.O = osum;
-    m.Q = qsum;
-    m.E = acc_E;
-    m.C = acc_C;
-    m.W = acc_W;
-    m.sum_completion = csum;
-    m.sum_latency = lsum;
-    m.sum_extent = acc_ext;
-    m.busy_steps = acc_busy;
-    m.peak_kv = acc_peak;
-    m.unfair_steps = acc_unf;
-    m.max_extent = acc_maxext;
-    m.max_active = acc_maxact;
+    m.Q = (int64_t)(r.q2 >> 1);  // every term is even
+    m.E = (int64_t)r.E;
+    m.C = c0 + a.c * (int64_t)r.D + a.tau * (int64_t)r.SSM;
+    m.W = c0 + a.c * (int64_t)r.D + a.tau * (int64_t)r.SM;
+    m.sum_completion = r.csum;
+    m.sum_latency = r.csum - r.asum;
+    m.sum_extent = (int64_t)r.X;
+    m.busy_steps = r.B;
+    m.peak_kv = r.P;
+    m.unfair_steps = r.U;
+    m.max_extent = r.Xm;
+    m.max_active = r.Am;
     a.out[inst] = m;
-    a.viol[inst] = v;
+    a.viol[inst] = r.v;
   }
 }
 
-hipError_t launch_decompose(const DecArgs& a, bool narrow, int wpb, size_t lds, hipStream_t s) {
-  const int64_t blocks = (a.n_inst + wpb - 1) / wpb;
-  if (narrow)
-    hipLaunchKernelGGL(decompose_kernel<true>, dim3((unsigned)blocks), dim3((unsigned)(wpb * WAVE)),
-                       lds, s, a);
-  else
-    hipLaunchKernelGGL(decompose_kernel<false>, dim3((unsigned)blocks),
-                       dim3((unsigned)(wpb * WAVE)), lds, s, a);
+hipError_t launch_decompose(const DecArgs& a0, hipStream_t s) {
+  DecArgs a = a0;
+  int NP2 = 64;
+  while (NP2 < 2 * a.n) NP2 <<= 1;
+  // sorted events, then the length of each job (16 bits); two waves also share
+  // their instance's totals
+  const int G = dec_waves(NP2);
+  a.wave_words = NP2 + (a.n + 1) / 2;
+  if (G > 1) a.wave_words = ((a.wave_words + 1) & ~1) + (int)sizeof(DecShared) / 4;
+  a.wave_words = (a.wave_words + (G > 1 ? 1 : 3)) & ~(G > 1 ? 1 : 3);
+  int wpb = G > 1 ? 1 : 4;  // instances per block
+  const size_t lds = (size_t)a.wave_words * 4 * wpb;
+  const dim3 grid((unsigned)((a.n_inst + wpb - 1) / wpb)), block((unsigned)(wpb * G * WAVE));
+#define FS_DEC(E)                                                                            \
+  case E: hipLaunchKernelGGL((decompose_kernel<E, dec_waves(E)>), grid, block, lds, s, a); break;
+  switch (NP2) {
+    FS_DEC(64)
+    FS_DEC(128)
+    FS_DEC(256)
+    FS_DEC(512)
+    FS_DEC(1024)
+    FS_DEC(2048)
+    FS_DEC(4096)
+    FS_DEC(8192)
+    default: return hipErrorInvalidValue;
+  }
+#undef FS_DEC
   return hipGetLastError();
 }
 

@@ -178,3 +178,35 @@ def test_pack_scan_batches(dev, n, B, alpha):
     for M in (0, 2 * B * alpha):
         check(dev, f"n={n} B={B} alpha={alpha} M={M}", a, z, o, policy="isjl", B=B, alpha=alpha,
               M_kv=M, cost_c=3, cost_tau=2)
+
+
+@pytest.mark.parametrize("n", [1, 32, 33, 64, 512, 513, 700, 1024, 1025, 2048, 2049, 4096])
+def test_rescoring_halves(dev, n):
+    """Re-scoring with one and with two waves per instance: groups across the middle of the sorted
+    events (every start or every end at one step, too), idle gaps, a second half with nothing
+    active before it, jobs of 65,536 tokens and more beside short ones, violations of every kind."""
+    import torch
+    import paper_2608_02244_amd as fs
+    rng = np.random.default_rng(n)
+    k = 9
+    size = (k, n)
+    a = rng.integers(0, 5, size=size).astype(np.int32)
+    p = rng.integers(0, 30, size=size).astype(np.int32)
+    o = rng.integers(1, 90, size=size).astype(np.int32)
+    s = (a + rng.integers(0, 3 * n + 1, size=size)).astype(np.int32)
+    s[1] = 7  # all start together
+    s[2] = 200 - (p[2] + o[2])  # all end together
+    s[3] = np.where(np.arange(n) % 2, 5, 400)  # two batches with a gap between them
+    p[4, : max(1, n // 2)] = 70000  # long jobs
+    s[5] = a[5] + rng.integers(0, 4, size=n)  # few distinct starts
+    p[6], o[6], s[6] = 0, 1, np.arange(n)  # one at a time
+    s[7] = np.sort(s[7])
+    s[8] = a[8] + 3 * rng.integers(0, n + 1, size=n)
+    for B, alpha, M in ((0, ALPHA_INF, 0), (3, 11, 500), (n, 0, 40 * n)):
+        log(f"rescoring n={n} B={B} alpha={alpha} M={M}")
+        t = [torch.from_numpy(np.ascontiguousarray(x)).to(dev) for x in (a, p, o, s)]
+        m, v = fs.cost_decompose(*t, B=B, alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
+        torch.cuda.synchronize()
+        rm, rv = oracle.decompose(a, p, o, s, B=B, alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
+        assert_same(f"rescoring n={n} B={B}", fs.metrics_view(m), rm)
+        assert np.array_equal(v.cpu().numpy().astype(np.uint32), rv)
