@@ -957,24 +957,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
             // each goes to the first spare worker with room, else to the long
             // worker of largest index with room; a job that fits nowhere stays.
             //
-            // The scan is a chain: each choice needs the rooms that the last one
-            // left.  64 candidates at a time are gathered, one per lane, so that a
-            // step is lane reads, one ballot per slot register and lane selects,
-            // with no memory access and no bitmap search; the batch's links and
-            // bitmap bits are written together after it.  A step that took its
-            // candidate from the bitmap and linked it at once cost about 750
-            // cycles with one wave per SIMD, 20 to 40 % of a wave's life (65,536 x
-            // 2,000 at B = 512: 3.72 -> 3.27 ms; 16,384 x 2,000 with the prompt
-            // prefilled, 890 steps per instance: 7.17 -> 5.73 ms).
+            // 64 candidates at a time are gathered, one per lane, and the workers
+            // are filled one by one in that order, each with the candidates left,
+            // longest first, that fit its room.  That is the same assignment:
+            // whether a candidate goes to a worker depends only on the longer ones
+            // that went there and on its having been refused by the workers before
+            // it.  A step is then one ballot, a lane read and a subtraction (the
+            // candidate-by-candidate scan chose among all workers at each step: 8
+            // ballots at 8 slots per lane, and 590 cycles per step even at one);
+            // the batch's links and bitmap bits are written together after it.
+            // 16,384 x 2,000 with the prompt prefilled, 890 steps per instance:
+            // 7.17 ms with a step per candidate straight from the bitmap, 5.73 from
+            // gathered candidates, 4.66 worker by worker.
             const bool has_spare = uni(Bp) > m;
-            uint64_t spare_m[K];
-            if constexpr (K <= 4) {
-#pragma unroll
-              for (int k = 0; k < K; ++k) {
-                const int w = k * WAVE + lane;
-                spare_m[k] = ballot((w >= m) & (w < Bp));
-              }
-            }
             auto largest_room = [&]() -> int {
               int rm = room[0];
 #pragma unroll
@@ -1013,54 +1008,57 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
               const int cl = lane < cnt ? plen(W[cr]) : 0;
               wave_lds_sync();  // the batch is out of the gather buffer
               int prev = (int)QNONE;  // the job before it in its worker's queue
-              uint64_t placed = 0;
-              uint64_t todo = cnt < WAVE ? (1ull << cnt) - 1 : ~0ull;
-              while (todo) {
-                const int i = __builtin_ctzll(todo);
-                const int len = readlane(cl, i);
-                int wsel = -1;
-                if (has_spare) {  // spare workers, ascending
-#pragma unroll
-                  for (int k = 0; k < K; ++k) {
-                    const int w = k * WAVE + lane;
-                    const uint64_t ms = K <= 4 ? ballot(room[k] >= len) & spare_m[k]
-                                               : ballot((w >= m) & (room[k] >= len));
-                    if (ms) {
-                      wsel = k * WAVE + __builtin_ctzll(ms);
-                      break;
-                    }
-                  }
-                }
-                if (wsel < 0) {  // long workers, largest index first (no spare has room)
-#pragma unroll
-                  for (int k = K - 1; k >= 0; --k) {
-                    const uint64_t ml = ballot(room[k] >= len);
-                    if (ml) {
-                      wsel = k * WAVE + 63 - __builtin_clzll(ml);
-                      break;
-                    }
-                  }
-                }
-                if (wsel < 0) {  // it fits nowhere: on to the first one that fits some room
-                  todo &= ballot(cl <= largest_room());
-                  continue;
-                }
-                todo &= todo - 1;
-                placed |= 1ull << i;
-                const int r = readlane(cr, i);
-                wsel = uni(wsel);  // the same in every lane (kept in a scalar register)
-                const int wl = wsel & (WAVE - 1);
+              const uint64_t all = cnt < WAVE ? (1ull << cnt) - 1 : ~0ull;
+              uint64_t left = all;
+              // worker w = k * 64 + b takes what fits, in order
+              auto fill_worker = [&](int& room_k, uint32_t& q_k, int b) {
+                int rm = readlane(room_k, b);
+                const uint32_t qq = (uint32_t)readlane((int)q_k, b);
+                int head_r = (int)(qq & 0xFFFFu), tail_r = (int)(qq >> 16);
+                uint64_t m_fit = ballot(cl <= rm) & left;
+                do {
+                  const int i = __builtin_ctzll(m_fit);
+                  rm -= readlane(cl, i);
+                  const int r = readlane(cr, i);
+                  prev = lane == i ? tail_r : prev;
+                  tail_r = r;
+                  if (head_r == (int)QNONE) head_r = r;
+                  left &= ~(1ull << i);
+                  m_fit &= m_fit - 1;  // those after it that still fit
+                  m_fit &= ballot(cl <= rm);
+                } while (m_fit);
+                room_k = lane == b ? rm : room_k;
+                q_k = lane == b ? (uint32_t)head_r | ((uint32_t)tail_r << 16) : q_k;
+              };
+              // the workers that fit the shortest candidate left (so each takes one)
+              auto shortest = [&]() -> int { return readlane(cl, 63 - __builtin_clzll(left)); };
+              if (has_spare) {  // spare workers, ascending
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                  if (k == (wsel >> 6)) {
-                    const uint32_t qq = (uint32_t)readlane((int)ws_q[k], wl);
-                    const uint32_t h = (qq & 0xFFFFu) == QNONE ? (uint32_t)r : qq & 0xFFFFu;
-                    prev = lane == i ? (int)(qq >> 16) : prev;
-                    ws_q[k] = lane == wl ? h | ((uint32_t)r << 16) : ws_q[k];
-                    room[k] -= lane == wl ? len : 0;
+                  const int w = k * WAVE + lane;
+                  uint64_t ws = ballot((w >= m) & (w < Bp));
+                  while (ws && left) {
+                    ws &= ballot(room[k] >= shortest());
+                    if (!ws) break;
+                    const int b = __builtin_ctzll(ws);
+                    ws &= ws - 1;
+                    fill_worker(room[k], ws_q[k], b);
                   }
                 }
               }
+#pragma unroll
+              for (int k = K - 1; k >= 0; --k) {  // long workers, largest index first
+                const int w = k * WAVE + lane;
+                uint64_t wl = ballot((w >= 1) & (w < m));
+                while (wl && left) {
+                  wl &= ballot(room[k] >= shortest());
+                  if (!wl) break;
+                  const int b = 63 - __builtin_clzll(wl);
+                  wl &= ~(1ull << b);
+                  fill_worker(room[k], ws_q[k], b);
+                }
+              }
+              const uint64_t placed = all & ~left;
               // the batch's links (a queue ends at its tail: the last one has none)
               // and its bits of the queued ranks
               const bool put = (placed >> lane) & 1ull;
