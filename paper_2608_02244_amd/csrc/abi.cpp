@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstdint>
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <mutex>
 
@@ -123,11 +124,32 @@ hipMemPool_t rank_pool(bool create = true) {
   return pools[dev];
 }
 
+// Compute units of the current device (looked up once per device), 0 if the
+// runtime cannot tell.
+int device_cus() {
+  constexpr int kMaxDev = 64;
+  static std::atomic<int> cus[kMaxDev] = {};
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  n = cus[dev].load(std::memory_order_relaxed);
+  if (n == 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+      (void)hipGetLastError();
+      return 0;
+    }
+    cus[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
+}
+
 size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Launch shape and scratch layout of one simulate call.
 struct SimLayout {
-  int Beff, K, NW, NP, q_words, stage_words;
+  int Beff, K, NW, NP, q_words, stage_words, n_cu;
   bool q_hbm;
   int32_t rank_stride;
   size_t rank_bytes, qlink_bytes;  // device scratch, each rounded up to 256 bytes
@@ -144,9 +166,11 @@ int simulate_layout(const fsched_params* p, int64_t n_inst, int32_t n, SimLayout
   // plan-queue links; with alpha = infinity Phase ONE never plans (no second
   // job is longer than alpha), so the links are not needed
   // (with up to 8 slots per lane, at most 128 VGPRs, 16 waves fit a CU: the
-  // links go to HBM scratch when in LDS they would cap a CU below that)
+  // links go to HBM scratch when in LDS they would cap a CU below that and the
+  // call has more instances than then fit the device)
   const bool plans = isjl && p->alpha != FSCHED_ALPHA_INF;
   bool q_hbm = false;
+  const int n_cu = device_cus();
   if (plans && K <= 8) {
     const int w_lds = NP + NP / 2 +
                       std::max((Beff + 1) / 2, 64 * NW);  // words per wave with the links
@@ -154,12 +178,13 @@ int simulate_layout(const fsched_params* p, int64_t n_inst, int32_t n, SimLayout
     int wpb = 4;
     while (wpb > 1 && per_wave * wpb > 64 * 1024) wpb >>= 1;
     const size_t waves_per_cu = (160 * 1024) / (per_wave * wpb) * wpb;
-    q_hbm = waves_per_cu < 16;
+    q_hbm = waves_per_cu < 16 && n_inst > (int64_t)waves_per_cu * n_cu;
   }
   L->Beff = Beff;
   L->K = K;
   L->NW = NW;
   L->NP = NP;
+  L->n_cu = n_cu;
   L->q_hbm = q_hbm;
   L->q_words = (plans && !q_hbm) ? NP / 2 : 0;
   // gather buffer (uint16 per worker), also the release scatter buffer (one
@@ -260,9 +285,14 @@ int launch_simulate(const fsched_params* p, int64_t n_inst, int32_t n, const int
   a.wave_words = a.off_stage + stage_words;
   a.wave_words = (a.wave_words + 3) & ~3;
   size_t per_wave = (size_t)a.wave_words * 4;
-  int wpb = 4;
+  // few instances: a CU of its own for each (the block's waves would share one).
+  // With the plan links in LDS and no priority turns below, 256 x 64 ISJL took
+  // 64.9 -> 59.2 us and 256 x 2,000 at B = 16 1,095 -> 988 us.
+  int wpb = n_inst <= Lay.n_cu ? 1 : n_inst <= 2 * (int64_t)Lay.n_cu ? 2 : 4;
   while (wpb > 1 && per_wave * wpb > 64 * 1024) wpb >>= 1;
   size_t lds = per_wave * wpb;
+  // with at most one wave per SIMD there is nothing to share issue slots with
+  a.share_simds = n_inst > 4 * (int64_t)Lay.n_cu ? 1 : 0;
   hipError_t err;
   const bool pre = (p->flags & FSCHED_F_PREFILL) != 0;
   switch (p->policy) {

@@ -30,6 +30,7 @@ struct SimArgs {
   int32_t off_stage;  // word offset of the gather / release buffer (not FCFS)
   int32_t resume;     // ISJL: Phase TWO resumes once A_max <= alpha (1) or waits
                       // for an empty machine (0)
+  int32_t share_simds;  // several of the launch's waves run on one SIMD
   const int32_t* arrival;
   const int32_t* prompt;
   const int32_t* output;

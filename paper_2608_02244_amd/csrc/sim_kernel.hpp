@@ -2025,7 +2025,8 @@ hipError_t launch_sim(const SimArgs& a, int K, int NW, int wpb, size_t lds, hipS
 #define FS_LAUNCH(KK, NN, FF, QQ)                                                         \
   if (K == KK && NW == NN && fill == FF && qh == QQ) {                                    \
     if constexpr (KK <= 8) {                                                              \
-      if (resident_at_once((const void*)simulate_kernel<POL, KK, NN, ROB, PRE, FF, QQ, true>, \
+      if (a.share_simds &&                                                                \
+          resident_at_once((const void*)simulate_kernel<POL, KK, NN, ROB, PRE, FF, QQ, true>, \
                            blocks, wpb, lds)) {                                           \
         hipLaunchKernelGGL((simulate_kernel<POL, KK, NN, ROB, PRE, FF, QQ, true>), grid, block, \
                            lds, s, a);                                                    \

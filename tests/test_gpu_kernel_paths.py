@@ -210,3 +210,23 @@ def test_rescoring_halves(dev, n):
         rm, rv = oracle.decompose(a, p, o, s, B=B, alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
         assert_same(f"rescoring n={n} B={B}", fs.metrics_view(m), rm)
         assert np.array_equal(v.cpu().numpy().astype(np.uint32), rv)
+
+
+@pytest.mark.parametrize("prefill", [False, True])
+@pytest.mark.parametrize("B", [16, 100, 200, 500])
+def test_plan_links_in_hbm_for_large_batches(dev, B, prefill):
+    """The plan-queue links move to HBM scratch only where the batch is larger than what the LDS
+    lets run at once (3,072 instances of 2,000 jobs): 3,200 copies of 8 instances, each copy
+    equal to the oracle's result."""
+    rng = np.random.default_rng(B)
+    a, p, o = (rng.integers(lo, hi, size=(8, 2000)).astype(np.int32)
+               for lo, hi in ((0, 300), (0, 40), (1, 200)))
+    a.sort(axis=1)
+    a[7] = rng.permutation(a[7])
+    kw = dict(policy="isjl", B=B, alpha=45, M_kv=70 * B, cost_c=3, cost_tau=2)
+    log(f"plan links in HBM B={B} prefill={prefill}")
+    got, gs, gf = gpu_sim(dev, *(np.tile(x, (400, 1)) for x in (a, p, o)), prefill=prefill, **kw)
+    ref, rs, rf = oracle.simulate(a, p, o, schedule=True,
+                                  flags=oracle.FLAG_PREFILL if prefill else 0, **kw)
+    assert_same(f"B={B}", got, np.tile(ref, 400), gs, np.tile(rs, (400, 1)), gf,
+                np.tile(rf, (400, 1)))
