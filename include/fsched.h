@@ -31,7 +31,9 @@
  *     NULL for the null stream); outputs are valid once the stream reaches the
  *     call.  Without the flag every array is host memory; the library stages
  *     through device memory it allocates and frees itself and returns after
- *     the results are back in host memory.
+ *     the results are back in host memory.  (A call whose arrays take at most
+ *     4 MiB in all takes that memory from the pool described below, which keeps
+ *     it until fsched_release_cache.)
  *   - The caller owns every buffer.  The library keeps no pointer after the
  *     call (host mode) or after the stream passes the call (device mode).
  *   - fsched_simulate, fsched_simulate_robust and fsched_bruteforce_opt (every

@@ -230,3 +230,54 @@ def test_plan_links_in_hbm_for_large_batches(dev, B, prefill):
                                   flags=oracle.FLAG_PREFILL if prefill else 0, **kw)
     assert_same(f"B={B}", got, np.tile(ref, 400), gs, np.tile(rs, (400, 1)), gf,
                 np.tile(rf, (400, 1)))
+
+
+def test_host_arrays_of_every_size_and_thread(dev):
+    """Host mode below, at and above the 4 MiB of the pool's arena, from several threads at
+    once, against device mode; an invalid table in between is still refused."""
+    import threading
+    import torch
+    import paper_2608_02244_amd as fs
+    errors = []
+
+    def work(seed):
+        try:
+            rng = np.random.default_rng(seed)
+            # rows of 1,000 jobs: 250 instances with schedules take 4.96 MB, 200 take 4.02 MB
+            for k, n in ((1, 1), (3, 70), (200, 1000), (209, 1000), (250, 1000)):
+                a = np.zeros((k, n), np.int32)
+                p = rng.integers(0, 20, size=(k, n)).astype(np.int32)
+                o = rng.integers(1, 50, size=(k, n)).astype(np.int32)
+                kw = dict(B=8, alpha=20, M_kv=300, cost_c=3, cost_tau=2)
+                t = [torch.from_numpy(x).to(dev) for x in (a, p, o)]
+                for policy in ("isjl", "fcfs"):
+                    m, s, f = fs.simulate(a, p, o, policy=policy, schedule=True, **kw)
+                    gm, gs, gf = fs.simulate(*t, policy=policy, schedule=True, **kw)
+                    assert np.array_equal(m, fs.metrics_view(gm))
+                    assert np.array_equal(s, gs.cpu().numpy())
+                    assert np.array_equal(f, gf.cpu().numpy())
+                    dm, dv = fs.cost_decompose(a, p, o, s, **kw)
+                    gdm, gdv = fs.cost_decompose(*t, gs, **kw)
+                    assert np.array_equal(dm, fs.metrics_view(gdm))
+                    assert np.array_equal(dv, gdv.cpu().numpy().astype(np.uint32))
+                bad = o.copy()
+                bad[-1, -1] = 0
+                with pytest.raises(fs.FschedError) as ei:
+                    fs.simulate(a, p, bad, policy="isjl", **kw)
+                assert ei.value.code == fs.EINVAL
+            q = rng.integers(1, 9, size=(500, 6)).astype(np.int32)
+            z = np.zeros_like(q)
+            T, st = fs.bruteforce_opt(z, z, q, B=2, alpha=2, schedule=True)
+            Tg, sg = fs.bruteforce_opt(*(torch.from_numpy(x).to(dev) for x in (z, z, q)), B=2,
+                                       alpha=2, schedule=True)
+            assert np.array_equal(T, Tg.cpu().numpy()) and np.array_equal(st, sg.cpu().numpy())
+        except Exception as e:  # noqa: BLE001  (reported by the main thread)
+            errors.append(repr(e))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    fs.release_cache()
