@@ -593,8 +593,67 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
   // (strict order; a job that would run alone always fits), onto the first
   // eligible idle workers in index order (ISJL Phase TWO also needs an empty
   // plan queue).  Returns the number admitted.
+  // Up to 64 jobs are read once, one per lane, and reach their slots through
+  // lane shuffles, with up to 2 slots per lane and wherever the prompts have to
+  // be looked up in the job table (16,384 x 2,000 with the prompt prefilled
+  // 4.68 -> 4.54 ms, 4,096 x 1,000 SJF at B = 64 0.283 -> 0.267 ms).  Longer
+  // batches, and the wide kernels without prompts (no gain there: 3.14 -> 3.15
+  // ms at B = 512), read them from LDS again by slot.
   auto admit_prefix = [&](int t, int G, bool need_empty_queue, int& adm,
-                          int& adm_minlen) -> int {
+                          int& adm_minlen) __attribute__((always_inline)) -> int {
+    if (K == 1 || ((K == 2 || PRE) && G <= WAVE)) {
+      const int r = lane < G ? (int)STG[lane] : 0;
+      const uint32_t wv = lane < G ? W[r] : 0u;
+      const int id = pid(wv), plan = plen(wv);
+      const int pp = (PRE && lane < G) ? P[id] : 0;
+      const int len = (ROB && lane < G) ? true_len(id, plan) : plan;
+      const int rv = plan + pp;  // reservation
+      const int pre = wave_scan_incl(rv);
+      int na = G;
+      if (M != 0) {
+        const uint64_t fm =
+            ballot((lane < G) & ((lane > 0) | (S.nact > 0)) & (S.res + pre > M));
+        if (fm) na = __builtin_ctzll(fm);
+      }
+      na = uni(na);
+      if (na == 0) return 0;
+      const bool inc = lane < na;
+      if (inc) emit(id, t, len);
+      int base = 0;
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        if (base < na) {
+          const bool el = valid[k] & (ws_end[k] == IDLE) &
+                          (!need_empty_queue | ((ws_q[k] & 0xFFFFu) == QNONE));
+          const uint64_t bm = ballot(el);
+          const int idx = base + mbcnt(bm);
+          const int src = min(idx, WAVE - 1);
+          const int l2 = __shfl(len, src);
+          const int r2 = (ROB || PRE) ? __shfl(rv, src) : 0, p2 = PRE ? __shfl(pp, src) : 0;
+          if (el & (idx < na)) {
+            ws_start[k] = t;
+            ws_end[k] = t + l2;
+            if (ROB || PRE) ws_plan[k] = r2;
+            if (PRE) ws_p[k] = p2;
+          }
+          base += __builtin_popcountll(bm);
+        }
+      }
+      // in priority order the shortest admitted job is the last (longest first)
+      // or the first (SJF), by planning size
+      adm_minlen = min(adm_minlen, ROB ? wave_min(inc ? len : IDLE)
+                                       : readlane(len, POL == POL_SJF ? 0 : na - 1));
+      if (PRE) {
+        S.sp += (uint32_t)wave_sum(inc ? pp : 0);
+        S.G = max(S.G, wave_max(inc ? pp : -IDLE) - t);  // na >= 1 jobs were admitted
+      }
+      pool.clear_upto(readlane(r, na - 1), lane);  // the first na queued ranks
+      qcount -= na;
+      adm += na;
+      S.res += readlane(pre, na - 1);
+      S.nact += na;
+      return na;
+    }
     int na = G;
     int ptot = -1;  // summed reservation of the admitted jobs, when the KV scan found it
     if (M != 0) {
@@ -677,14 +736,58 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
     return na;
   };
 
+  // Admit the first queued job if the KV budget lets it in (the usual case of one
+  // completion freeing one worker): no gather and no scan.
+  auto admit_one = [&](int t, bool need_empty_queue, int& adm, int& adm_minlen)
+                       __attribute__((always_inline)) -> int {
+    const int r = pool.first();
+    const uint32_t wv = uniu(W[r]);
+    const int id = pid(wv), plan = plen(wv);
+    const int pp = PRE ? uni(P[id]) : 0;
+    const int rv = plan + pp;
+    if (M != 0 && S.nact > 0 && S.res + rv > M) return 0;
+    const int len = ROB ? uni(true_len(id, plan)) : plan;
+    if (lane == 0) emit(id, t, len);
+    int at = -1;  // the first eligible worker
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (at < 0) {
+        const bool el = valid[k] & (ws_end[k] == IDLE) &
+                        (!need_empty_queue | ((ws_q[k] & 0xFFFFu) == QNONE));
+        const uint64_t bm = ballot(el);
+        if (bm) at = k * WAVE + __builtin_ctzll(bm);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const bool here = at == k * WAVE + lane;
+      ws_start[k] = here ? t : ws_start[k];
+      ws_end[k] = here ? t + len : ws_end[k];
+      if (ROB || PRE) ws_plan[k] = here ? rv : ws_plan[k];
+      if (PRE) ws_p[k] = here ? pp : ws_p[k];
+    }
+    adm_minlen = min(adm_minlen, len);
+    if (PRE) {
+      S.sp += (uint32_t)pp;
+      S.G = max(S.G, pp - t);
+    }
+    pool.reset(r, lane);
+    qcount -= 1;
+    adm += 1;
+    S.res += rv;
+    S.nact += 1;
+    return 1;
+  };
+
   // Gather and admit the strict prefix of the first G queued jobs.  With up to 4
   // slots per lane and a binding KV budget, the first 8 are gathered and scanned
   // alone and the rest only if all 8 fit: admitting those 8 and then the prefix
   // of the next G - 8 is the same strict prefix, and a budget that stops early
   // spares the gather of all G.
   auto admit_first = [&](int t, int G, bool need_empty_queue, int& adm,
-                         int& adm_minlen) -> int {
+                         int& adm_minlen) __attribute__((always_inline)) -> int {
     constexpr int G0 = 8;
+    if (K <= 2 && G == 1) return admit_one(t, need_empty_queue, adm, adm_minlen);
     if (K <= 4 && M != 0 && S.nact > 0 && G > G0) {
       gather_first(G0);
       const int na = admit_prefix(t, G0, need_empty_queue, adm, adm_minlen);
@@ -1176,7 +1279,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
               ws_end[k] = t + len;
               if (ROB || PRE) ws_plan[k] = clen[k];
               if (PRE) {
-                const int pp = P[pid(wv)];
+                const int pp = clen[k] - plan;  // reservation less planning size
                 ws_p[k] = pp;
                 lp += pp;
                 lpmax = max(lpmax, pp);
