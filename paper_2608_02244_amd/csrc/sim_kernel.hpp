@@ -204,10 +204,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
   extern __shared__ uint32_t lds_raw[];
   // With 4 or 8 slots per lane (but FCFS) the wave's index in its block is
   // taken into a scalar register: every row pointer derived from the instance
-  // is then scalar, which is what brings those kernels under 128 VGPRs (the
-  // narrower kernels ran slower with it, their scalar registers being the
-  // scarcer ones).
-  constexpr bool WIB_S = (K == 4 || K == 8) && POL != POL_FCFS;
+  // is then scalar, which is what brings those kernels under 128 VGPRs.  With one
+  // slot per lane it shortens the event loop's address chains (256 x 2,000 ISJL
+  // at B = 16: 918 -> 901 us); the kernels with two ran slower with it (445 ->
+  // 451 us at B = 128), their scalar registers being the scarcer ones.
+  constexpr bool WIB_S = K <= 8 && K != 2 && POL != POL_FCFS;
   const int wib = WIB_S ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
                         : (int)(threadIdx.x >> 6);
   const int64_t inst = (int64_t)blockIdx.x * (blockDim.x >> 6) + wib;
@@ -473,6 +474,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
   // deferral changes no result, and a sweep ends without a reduction.  The
   // wider kernels have no registers to spare for them and reduce per sweep.
   constexpr bool DEFER = K <= 2;
+  constexpr bool PLAN_RUN = POL == POL_ISJL && !FILL && K <= 2;
   SpanSums lane_sums;
   lane_sums.clear();
   auto reduce_lane_sums = [&](const SpanSums& l) {
@@ -821,7 +823,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
   // event count shares the issue slots among the SIMD's waves instead.
   int fair_turn = FAIR ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
   while (true) {
-    const int t = S.t;
+    int t = S.t;
     if constexpr (FAIR) {
       switch (fair_turn++ & 3) {
         case 0: __builtin_amdgcn_s_setprio(0); break;
@@ -1353,6 +1355,117 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
     const bool w0_timer = POL == POL_ISJL && planned > 0 && t_w1 > t &&
                           readlane(ws_end[0], 0) == IDLE &&
                           ((uint32_t)readlane((int)ws_q[0], 0) & 0xFFFFu) != QNONE;
+
+    // Plan run (ISJL with jobs planned).  While every worker is busy, each
+    // completion only starts the next planned job of its own worker, if the
+    // guard and the KV budget allow: no release, queue or mode is read (a worker
+    // left without a plan, a blocked start or worker 1's start time ends the
+    // run, before the event).  The same holds with workers idle when Phase TWO
+    // has stopped (DRAIN), or when it is held back by the KV budget: its first
+    // job only gets longer by releases, so it stays blocked while the
+    // reservations leave no room for the one queued now, up to the step where
+    // A_max passes alpha.  Up to three quarters of the events with a binding alpha
+    // are of this kind (4,096 x 2,000 at B = 128, alpha = 256: 593 -> 446 us; one
+    // instance of 200 jobs at B = 50: 148 -> 111 us).  Up to 2 slots per lane: the
+    // wide kernels ran no faster (3.13 ms at B = 512) or slower (4.51 -> 4.86 ms
+    // with the prompt prefilled, 0.93 -> 0.99 ms with predicted sizes).
+    if constexpr (PLAN_RUN) {
+      const int spare = Beff - S.nact - (w0_timer ? 1 : 0);  // idle, but worker 1 on its timer
+      const bool p2 = mode == 0 && spare > 0;
+      if (planned >= 4 && S.nact > 0 && !(mode == 1 && a.resume) &&
+          (!p2 || (!PRE && kv_block && qcount > 0))) {
+        uint64_t held = 0;  // idle workers with a blocked planned job
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          uint64_t h = ballot(valid[k] & (ws_end[k] == IDLE) & ((ws_q[k] & 0xFFFFu) != QNONE));
+          if (k == 0 && w0_timer) h &= ~1ull;
+          held |= h;
+        }
+        if (!held) {
+          const int p2len = p2 ? uni(plen(W[pool.first()])) : 0;
+          while (true) {
+            const int te = S.min_end;
+            if ((w0_timer && te >= t_w1) || (p2 && te - S.min_s > alpha + 1)) break;
+            int mn = IDLE;
+            bool none = false;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+              none |= (ws_end[k] == te) & ((ws_q[k] & 0xFFFFu) == QNONE);
+              mn = min(mn, ws_end[k] == te ? IDLE : ws_start[k]);
+            }
+            if (ballot(none)) break;
+            mn = wave_min(mn);
+            if (mn == IDLE || te - mn > alpha) break;
+            int ds = 0, dr = 0, cnt = 0;
+            uint32_t wv[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+              const bool c = ws_end[k] == te;
+              wv[k] = c ? W[ws_q[k] & 0xFFFFu] : 0u;
+              const int rv = c ? resv_len(pid(wv[k]), plen(wv[k])) : 0;
+              dr += c ? rv - ((ROB || PRE) ? ws_plan[k] : te - ws_start[k]) : 0;
+              ds += c ? te - ws_start[k] : 0;
+              cnt += __builtin_popcountll(ballot(c));
+            }
+            const int dres = M != 0 ? wave_sum(dr) : 0;
+            if (M != 0 && (S.res + dres > M || (p2 && S.res + dres + p2len <= M))) break;
+            account(te - S.t);
+            S.sum_s += (uint32_t)wave_sum(ds);
+            int me = IDLE, dp = 0, gm = -IDLE;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+              if (ws_end[k] == te) {
+                const uint32_t tl = ws_q[k] >> 16, h = ws_q[k] & 0xFFFFu;
+                const int id = pid(wv[k]), plan = plen(wv[k]);
+                const int len = true_len(id, plan);
+                if (ROB || PRE) {
+                  const int rv = resv_len(id, plan);
+                  if (PRE) {
+                    dp += (rv - plan) - ws_p[k];
+                    ws_p[k] = rv - plan;
+                  }
+                  ws_plan[k] = rv;
+                }
+                ws_start[k] = te;
+                ws_end[k] = te + len;
+                emit(id, te, len);
+                uint32_t nx;
+                if constexpr (QGLOBAL) {  // loaded ahead, as in the planned starts
+                  nx = ws_qn[k];
+                  ws_qn[k] = (nx != QNONE) & (nx != tl) ? qn_get((int)nx) : QNONE;
+                } else {
+                  nx = h != tl ? qn_get((int)h) : QNONE;
+                }
+                ws_q[k] = nx == QNONE ? (QNONE | (QNONE << 16)) : (nx | (tl << 16));
+              }
+              me = min(me, ws_end[k]);
+              if (PRE) gm = max(gm, ws_end[k] != IDLE ? ws_p[k] - ws_start[k] : -IDLE);
+            }
+            if (PRE) {
+              S.sp += (uint32_t)wave_sum(dp);
+              S.G = wave_max(gm);
+            }
+            S.min_s = mn;
+            S.max_s = te;
+            S.min_end = wave_min(me);
+            S.res += dres;
+            mac(S.sum_start, (uint32_t)cnt, (uint32_t)te);
+            S.ndone += cnt;
+            planned -= cnt;
+            S.t = te;
+            if (++iter > iter_max) break;
+          }
+          if (iter > iter_max) {
+            failed = true;
+            break;
+          }
+          // behind a blocked head the releases meanwhile are looked at first;
+          // otherwise they matter no more than before
+          if (p2 && S.t > t) continue;
+          t = S.t;
+        }
+      }
+    }
 
     // Release sweep (not LJF, which admits at an empty machine only; not with the
     // prompt prefilled, where the next completion is too close: 16,384 x 2,000

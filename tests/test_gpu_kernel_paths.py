@@ -281,3 +281,54 @@ def test_host_arrays_of_every_size_and_thread(dev):
         t.join()
     assert not errors, errors
     fs.release_cache()
+
+
+@pytest.mark.parametrize("resume", [False, True])
+@pytest.mark.parametrize("B,alpha", [(2, 9), (8, 30), (16, 100), (64, 40), (65, 25), (128, 200)])
+def test_plan_runs(dev, B, alpha, resume):
+    """Runs of planned starts: every worker busy, worker 1 on its timer, workers idle in DRAIN or
+    behind a head that the KV budget holds back (with releases meanwhile), ended by a worker
+    without a plan, by the guard or by the budget; several completions at one step."""
+    rng = np.random.default_rng(B + alpha)
+    n = 300
+    size = (24, n)
+    short = rng.integers(1, max(2, alpha // 4), size=size)
+    grid = (alpha // 5 + 1) * rng.integers(1, 4, size=size)  # many completions at one step
+    long = rng.integers(alpha + 1, 6 * alpha + 5, size=size)
+    u = rng.random(size)
+    share = np.linspace(0.3, 0.95, 24)[:, None]
+    o = np.where(u < share, np.where(rng.random(size) < 0.5, short, grid), long).astype(np.int32)
+    p = np.zeros(size, np.int32)
+    a = np.zeros(size, np.int32)
+    a[8:16] = np.sort(rng.integers(0, 4 * alpha, size=(8, n)), axis=1)
+    a[16:] = rng.integers(0, 40 * alpha, size=(8, n))
+    ref_flags = oracle.FLAG_RESUME_FILL if resume else 0
+    for M in (0, 3 * B * alpha, B * alpha, 9 * alpha):
+        ctx = f"B={B} alpha={alpha} M={M} resume={resume}"
+        log(ctx)
+        kw = dict(policy="isjl", B=B, alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
+        got, gs, gf = gpu_sim(dev, a, p, o, resume_fill=resume, **kw)
+        ref, rs, rf = oracle.simulate(a, p, o, schedule=True, flags=ref_flags, **kw)
+        assert_same(ctx, got, ref, gs, rs, gf, rf)
+
+
+def test_plan_runs_with_predicted_sizes(dev):
+    import torch
+    import paper_2608_02244_amd as fs
+    rng = np.random.default_rng(3)
+    size = (16, 250)
+    z = np.zeros(size, np.int32)
+    o = np.where(rng.random(size) < 0.8, rng.integers(1, 20, size=size),
+                 rng.integers(60, 300, size=size)).astype(np.int32)
+    u = (o + (rng.random(size) * o).astype(np.int32)).astype(np.int32)
+    for B, M in ((8, 0), (16, 900), (100, 4000)):
+        for prefill in (False, True):
+            log(f"predicted sizes B={B} M={M} prefill={prefill}")
+            p = rng.integers(0, 9, size=size).astype(np.int32) if prefill else z
+            kw = dict(B=B, alpha=50, M_kv=M, cost_c=3, cost_tau=2)
+            t = [torch.from_numpy(x).to(dev) for x in (z, p, o, u)]
+            m, s, f = fs.simulate_robust(*t, schedule=True, prefill=prefill, **kw)
+            rm, rs, rf = oracle.simulate_robust(z, p, o, u, schedule=True,
+                                                flags=oracle.FLAG_PREFILL if prefill else 0, **kw)
+            assert_same(f"B={B} M={M}", fs.metrics_view(m), rm, s.cpu().numpy(), rs,
+                        f.cpu().numpy(), rf)
