@@ -332,3 +332,28 @@ def test_plan_runs_with_predicted_sizes(dev):
                                                 flags=oracle.FLAG_PREFILL if prefill else 0, **kw)
             assert_same(f"B={B} M={M}", fs.metrics_view(m), rm, s.cpu().numpy(), rs,
                         f.cpu().numpy(), rf)
+
+
+@pytest.mark.parametrize("policy,alpha", [("fcfs", ALPHA_INF), ("sjf", ALPHA_INF), ("isjl", 0),
+                                          ("isjl", 12), ("isjl", 60), ("isjl", ALPHA_INF)])
+@pytest.mark.parametrize("n,B,rate", [(65, 40, 3), (129, 128, 30), (300, 130, 9), (700, 512, 8),
+                                      (900, 1000, 4)])
+def test_releases_among_completions_with_prefill(dev, policy, alpha, n, B, rate):
+    """Prompts prefilled: runs of releases with completions between them (at the same step too),
+    jobs that complete inside the run, the earliest or the latest started job ending in it, the
+    largest footprint's holder ending in it, more than 64 completions, workers freed in it."""
+    rng = np.random.default_rng(n + B + rate)
+    k = 18
+    gap = (rng.random((k, n)) < 1.0 / rate) * rng.integers(1, 4, size=(k, n))
+    a = np.cumsum(gap, axis=1).astype(np.int32)
+    o = rng.integers(1, 30, size=(k, n)).astype(np.int32)
+    o[3:6] = rng.integers(8, 14, size=(3, n))  # many completions, few inside a run
+    o[6:9] = np.where(rng.random((3, n)) < 0.1, 200, o[6:9])
+    o[9] = 10
+    o[10] = 1 + np.arange(n) % 40
+    p = rng.integers(0, 400, size=(k, n)).astype(np.int32)
+    p[1::3] = rng.integers(0, 9, size=p[1::3].shape)
+    a[-1] = rng.permutation(a[-1])
+    for M in (0, 200 * B, 20 * B + 400):
+        check(dev, f"{policy} alpha={alpha} n={n} B={B} M={M}", a, p, o, prefill=True,
+              policy=policy, B=B, alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
