@@ -194,6 +194,9 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
     return wide ? P[i] + O[i] : (int)LEN[i];
   };
 
+  // The sorted events lie at their bank-free places (swz): in order, the lanes'
+  // 32 consecutive events each met in one bank (2.98e8 conflict cycles per launch
+  // of 65,536 x 2,000; 2.81 -> 2.61 ms without them).
   // ---- events (keys written above) ---------------------------------------------
   sync();
   {
@@ -223,7 +226,7 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
       wave_lds_sync();
     }
 #pragma unroll
-    for (int k = 0; k < KS; ++k) mine[lane * KS + k] = key[k];
+    for (int k = 0; k < KS; ++k) mine[swz(lane * KS + k)] = key[k];
   }
   sync();
 
@@ -263,7 +266,7 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
   int lXm = 0, lAm = 0;
   bool over = false, lkv = false, lunf = false;
   // idle steps before the first event
-  const int t_first = (int)(EV[0] >> 13);
+  const int t_first = (int)(EV[swz(0)] >> 13);
   const int64_t c0 = a.c * (int64_t)t_first;
 
   // position of the k-th set bit (k >= 1) of m, which has at least k
@@ -334,7 +337,7 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
     int bnd = NE;
     for (int q = n; q < NE; q += WAVE) {
       const int e = q + lane;
-      const uint64_t m = ballot(e < NE && (EV[e] >> 13) != (EV[e - 1] >> 13));
+      const uint64_t m = ballot(e < NE && (EV[swz(e)] >> 13) != (EV[swz(e - 1)] >> 13));
       if (m) {
         bnd = q + __builtin_ctzll(m);
         break;
@@ -348,11 +351,11 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
         // the state before it: a job started earlier is active when it ends at
         // that time or later; nmin = nmax = 0 has the first group end search the
         // earliest and latest start, from the first and last such start event
-        const int tb = (int)(uniu(EV[bnd]) >> 13);
+        const int tb = (int)(uniu(EV[swz(bnd)]) >> 13);
         int cnt = 0, first = IDLE32, last = -1;
         uint32_t ss = 0, sr = 0;
         for (int e = lane; e < bnd; e += WAVE) {
-          const uint32_t key = EV[e];
+          const uint32_t key = EV[swz(e)];
           const int len = len_of(key), t = (int)(key >> 13);
           const bool on = ((key >> 12) & 1u) & (uint32_t)(t + len >= tb);
           cnt += on ? 1 : 0;
@@ -367,14 +370,14 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
         if (c_cnt > 0) {
           pmin = wave_min(first);
           pmax = wave_max(last);
-          min_s = (int)(uniu(EV[pmin]) >> 13);
-          max_s = (int)(uniu(EV[pmax]) >> 13);
+          min_s = (int)(uniu(EV[swz(pmin)]) >> 13);
+          max_s = (int)(uniu(EV[swz(pmax)]) >> 13);
         }
       }
     }
   }
   // keys and lengths are loaded one chunk ahead
-  uint32_t nkey = p0 + lane < NE ? EV[p0 + lane] : 0xFFFFFFFFu;
+  uint32_t nkey = p0 + lane < NE ? EV[swz(p0 + lane)] : 0xFFFFFFFFu;
   int nlen = p0 + lane < NE ? len_of(nkey) : 0;
 
   for (int base = p0; base < p1; base += WAVE) {
@@ -383,7 +386,7 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
     const uint32_t key = nkey;
     const int len = nlen;
     const int pn = p + WAVE;
-    nkey = pn < NE ? EV[pn] : 0xFFFFFFFFu;
+    nkey = pn < NE ? EV[swz(pn)] : 0xFFFFFFFFu;
     const int t = (int)(key >> 13);
     const bool is_start = valid & (((key >> 12) & 1u) != 0u);
     const bool is_end = valid & (((key >> 12) & 1u) == 0u);
@@ -540,7 +543,7 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
               bool ok = false;
               int st_time = 0;
               if (ee >= 0 && ee <= gpos) {
-                const uint32_t kk = EV[ee];
+                const uint32_t kk = EV[swz(ee)];
                 st_time = (int)(kk >> 13);
                 ok = ((kk >> 12) & 1u) && st_time + len_of(kk) > tg;
               }
@@ -570,7 +573,7 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
               bool ok = false;
               int st_time = 0;
               if (ee >= 0) {
-                const uint32_t kk = EV[ee];
+                const uint32_t kk = EV[swz(ee)];
                 st_time = (int)(kk >> 13);
                 ok = ((kk >> 12) & 1u) && st_time + len_of(kk) > tg;
               }

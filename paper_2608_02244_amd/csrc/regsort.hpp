@@ -200,8 +200,14 @@ __device__ __forceinline__ void reg_sort_payload(uint32_t (&key)[KS], int (&val)
   }
 }
 
-// Sort W[0 .. 64*KS) ascending through registers (W is read in any order and
-// written back sorted).
+// Place in LDS of position p of a sorted array: each block of 32 is permuted by
+// its own number, so that lanes that hold 32 consecutive positions each write to
+// different banks (in order they share one), and 64 consecutive positions still
+// lie in different ones (two per bank).
+__device__ __forceinline__ int swz(int p) { return p ^ ((p >> 5) & 31); }
+
+// Sort W[0 .. 64*KS) ascending through registers (W is read in any order; sorted
+// position p is written to W[swz(p)]).
 template <int KS, bool MED3 = false>
 __device__ inline void wave_reg_sort(uint32_t* W, int lane) {
   uint32_t key[KS];
@@ -210,7 +216,7 @@ __device__ inline void wave_reg_sort(uint32_t* W, int lane) {
   reg_sort_keys<KS, MED3>(key, lane);
   wave_lds_sync();
 #pragma unroll
-  for (int k = 0; k < KS; ++k) W[lane * KS + k] = key[k];
+  for (int k = 0; k < KS; ++k) W[swz(lane * KS + k)] = key[k];
 }
 
 }  // namespace fs

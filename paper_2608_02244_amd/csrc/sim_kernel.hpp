@@ -380,9 +380,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
     }
     wave_lds_sync();
     // each job's rank goes to the rank table for the release chunks (only this
-    // wave touches its row)
+    // wave touches its row); the keys come from their bank-free places, two blocks
+    // of 32 at a time, which are rewritten in order once read
     for (int r = lane; r < n; r += WAVE) {
-      uint32_t key = W[r];
+      uint32_t key = W[swz(r)];
       int id = (int)(key & 0xFFFu);
       uint32_t len;
       if (POL == POL_LJF || POL == POL_ISJL) len = LMASK - (key >> 12);
