@@ -832,32 +832,33 @@ __global__ __launch_bounds__(64) void opt_clear_kernel(int32_t* counters, int n)
   if ((int)threadIdx.x < n) counters[threadIdx.x] = 0;
 }
 
-// One wave per instance of the batch, or (with todo_list) waves that take the
-// listed instances one at a time until the list is exhausted.
+// One wave per instance of the batch, or of the list (whose length only the
+// device knows: the blocks beyond it end at once).  A loop over the list around
+// the search cost it scalar registers and 5-9 % of its time; a constant LDS
+// base, which the compiler keeps in scalar registers too (245 instead of 192 of
+// them spilled), 3 %.
 __global__ __launch_bounds__(64) void opt_kernel(OptArgs a) {
   extern __shared__ uint32_t lds_raw[];
   const int lane = lane_id();
-  uint32_t* base = lds_raw;
+  const int wib = threadIdx.x >> 6;
+  uint32_t* base = lds_raw + wib * (MEMO_BYTES / 4 + FRAMES * FW + FRAMES * CACHE);
   uint32_t* frames = base + MEMO_BYTES / 4;
   uint32_t* keys = frames + FRAMES * FW;
-  const int nlist = a.todo_list ? __hip_atomic_load(a.todo_count, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT)
-                                : 0;
+
   int64_t inst = blockIdx.x;
-  while (true) {
-    if (a.todo_list) inst = claim(a.todo_list, a.todo_count, nlist, lane);
-    if (inst < 0) break;
-    Inst I;
-    if (a.T[inst] >= 0 /* else ISJL's error marker */ && load_inst(a, inst, lane, I)) {
-      Memo memo{base, I.compact, false, I.compact ? MEMO_BYTES / 8 : MEMO_BYTES / 16};
-      memo.clear(lane);
-      if (!solve(a, inst, I, memo, frames, keys, lane, GUARD)) {
-        // the LDS memo was too small for this search: leave it to the second pass
-        if (a.fb_list) append(a.fb_list, a.fb_count, inst, lane);
-        else if (lane == 0) a.T[inst] = FSCHED_T_INTERNAL;
-      }
-    }
-    if (!a.todo_list) break;
+  if (a.todo_list) {
+    if (inst >= *a.todo_count) return;
+    inst = a.todo_list[inst];
+  }
+  if (a.T[inst] < 0) return;  // ISJL's error marker
+  Inst I;
+  if (!load_inst(a, inst, lane, I)) return;
+  Memo memo{base, I.compact, false, I.compact ? MEMO_BYTES / 8 : MEMO_BYTES / 16};
+  memo.clear(lane);
+  if (!solve(a, inst, I, memo, frames, keys, lane, GUARD)) {
+    // the LDS memo was too small for this search: leave it to the second pass
+    if (a.fb_list) append(a.fb_list, a.fb_count, inst, lane);
+    else if (lane == 0) a.T[inst] = FSCHED_T_INTERNAL;
   }
 }
 
@@ -906,7 +907,6 @@ hipError_t launch_pair(const OptArgs& a, int64_t blocks, int entries, int32_t* s
 hipError_t launch_opt(const OptArgs& a0, hipStream_t s) {
   OptArgs a = a0;
   const size_t lds = (size_t)opt_lds_words_per_wave() * 4;
-  int64_t blocks = a.n_inst;
   if (a.lists) {
     hipLaunchKernelGGL(opt_clear_kernel, dim3(1), dim3((unsigned)WAVE), 0, s, a.counters,
                        OPT_COUNTERS);
@@ -941,10 +941,9 @@ hipError_t launch_opt(const OptArgs& a0, hipStream_t s) {
       // the search takes what is left (releases, larger tables)
       a.todo_list = list;
       a.todo_count = list_n;
-      blocks = std::min<int64_t>(a.n_inst, 1024);  // the waves that its LDS lets run at once
     }
   }
-  hipLaunchKernelGGL(opt_kernel, dim3((unsigned)blocks), dim3((unsigned)WAVE), lds, s, a);
+  hipLaunchKernelGGL(opt_kernel, dim3((unsigned)a.n_inst), dim3((unsigned)WAVE), lds, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !a.lists) return e;
   hipLaunchKernelGGL(opt_fallback_kernel, dim3((unsigned)OPT_FB_WAVES), dim3((unsigned)WAVE),
