@@ -11,7 +11,7 @@
 namespace fs {
 
 // Bytes of device scratch one fsched_simulate call of this shape needs (the
-// rank table and, for ISJL with up to 128 workers, the plan-queue links).
+// rank table and, where they are kept there, the plan-queue links).
 int simulate_scratch_need(const fsched_params* p, int64_t n_inst, int32_t n_jobs,
                           size_t* bytes);
 
