@@ -239,9 +239,11 @@ int simulate_layout(const fsched_params* p, int64_t n_inst, int32_t n, SimLayout
   // gather buffer (uint16 per worker), also the release scatter buffer (one
   // word per 32 ranks)
   // FCFS gathers nothing, but with 2 or more slots per lane its sweeps pack up to
-  // 64 active slots through this buffer too
-  L->stage_words =
-      p->policy != FSCHED_FCFS ? std::max((Beff + 1) / 2, 64 * NW) : (K >= 2 ? 64 : 0);
+  // 64 active slots through this buffer too, and with the prompt prefilled its
+  // release sweep packs up to 64 completions whatever the slots
+  const bool pre = (p->flags & FSCHED_F_PREFILL) != 0;
+  L->stage_words = p->policy != FSCHED_FCFS ? std::max((Beff + 1) / 2, 64 * NW)
+                                            : (K >= 2 || pre ? 64 : 0);
   L->rank_stride = (n + 63) & ~63;
   // the rank table of the release chunks (not FCFS, whose order is the arrival
   // order) and the HBM plan-queue links

@@ -357,3 +357,16 @@ def test_releases_among_completions_with_prefill(dev, policy, alpha, n, B, rate)
     for M in (0, 200 * B, 20 * B + 400):
         check(dev, f"{policy} alpha={alpha} n={n} B={B} M={M}", a, p, o, prefill=True,
               policy=policy, B=B, alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
+
+
+def test_releases_among_completions_in_full_blocks(dev):
+    """FCFS with one slot per lane, prompts prefilled, in blocks of several instances: each one's
+    completions are packed in a place of its own."""
+    rng = np.random.default_rng(33)
+    k, n = 1100, 150
+    a = np.cumsum(rng.integers(0, 3, size=(k, n)), axis=1).astype(np.int32)
+    o = np.minimum(8 * (1 - rng.random((k, n))) ** -0.6, 900).astype(np.int32)
+    p = rng.integers(1, 1500, size=(k, n)).astype(np.int32)
+    for B, M in ((33, 0), (64, 30000)):
+        check(dev, f"B={B} M={M}", a, p, o, prefill=True, policy="fcfs", B=B, alpha=64, M_kv=M,
+              cost_c=3, cost_tau=2)
