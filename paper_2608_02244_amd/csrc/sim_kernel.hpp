@@ -1628,8 +1628,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
     // two registers) into at most 128 events; the jobs active after each event are
     // the others, the completions after it and the releases up to it: prefix sums,
     // a suffix maximum and a prefix maximum.  16,384 x 2,000 ISJL, where such steps
-    // were some 130 of 324 events per instance: 4.59 -> 4.10 ms.
-    if constexpr (PRE && POL != POL_LJF) {
+    // were some 130 of 324 events per instance: 4.59 -> 4.10 ms.  Not with 16 slots
+    // per lane, where its registers leave one wave per SIMD instead of two: 2,048 x
+    // 1,500 ISJL at B = 1000, alpha = 0 took 0.79 ms with it, 0.45 without.
+    if constexpr (PRE && POL != POL_LJF && K <= 8) {
       const int F = Beff - S.nact;
       if ((POL == POL_FCFS ? head == relk : qcount == 0) && relk < n && S.nact > 1 && F > 0 &&
           (POL != POL_ISJL || (mode == 0 && planned == 0))) {
