@@ -2431,7 +2431,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
                        ((uint32_t)readlane((int)ws_q[0], 0) & 0xFFFFu) != QNONE;
         if (w0_wait) tn = min(tn, t_w1);
       }
-      if (mode == 0 && kv_block && alpha != IDLE) tn = min(tn, S.min_s + alpha + 1);
+      // (unsigned: any two steps below 2^31 and the one beyond them fit, so an alpha
+      // near 2^31, or infinity, leaves tn as it is)
+      if (mode == 0 && kv_block)
+        tn = (int)min((uint32_t)tn, (uint32_t)S.min_s + (uint32_t)alpha + 1u);
     }
     if (tn == IDLE || tn <= t || ++iter > iter_max) {
       failed = true;

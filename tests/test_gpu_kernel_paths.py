@@ -370,3 +370,57 @@ def test_releases_among_completions_in_full_blocks(dev):
     for B, M in ((33, 0), (64, 30000)):
         check(dev, f"B={B} M={M}", a, p, o, prefill=True, policy="fcfs", B=B, alpha=64, M_kv=M,
               cost_c=3, cost_tau=2)
+
+
+@pytest.mark.parametrize("alpha", [1 << 30, (1 << 31) - 1000, (1 << 31) - 2])
+@pytest.mark.parametrize("B", [2, 64, 65, 130, 300, 520])
+def test_finite_fairness_budgets_up_to_the_largest(dev, B, alpha):
+    """A finite alpha beyond every length, up to the largest (2^31 - 2), while the KV budget holds
+    Phase TWO back: A_max never passes it, and the step where it would lies beyond 2^31."""
+    import torch
+    import paper_2608_02244_amd as fs
+    rng = np.random.default_rng(B)
+    n = B + 40
+    size = (6, n)
+    a = np.sort(rng.integers(0, 90, size=size), axis=1).astype(np.int32)
+    a[0] = 0
+    a[1] = rng.permutation(a[1])
+    p = rng.integers(0, 30, size=size).astype(np.int32)
+    o = rng.integers(1, 60, size=size).astype(np.int32)
+    o[2, :: 7] = 900  # jobs that run alone
+    u = (o + rng.integers(0, 20, size=size)).astype(np.int32)
+    for M in (60, 12 * B + 50):
+        kw = dict(B=B, alpha=alpha, M_kv=M, cost_c=3, cost_tau=2)
+        for prefill in (False, True):
+            check(dev, f"B={B} alpha={alpha} M={M} prefill={prefill}", a, p, o, prefill=prefill,
+                  policy="isjl", **kw)
+            t = [torch.from_numpy(x).to(dev) for x in (a, p, o, u)]
+            m, s, f = fs.simulate_robust(*t, schedule=True, prefill=prefill, **kw)
+            rm, rs, rf = oracle.simulate_robust(a, p, o, u, schedule=True,
+                                                flags=oracle.FLAG_PREFILL if prefill else 0, **kw)
+            assert_same(f"robust B={B} alpha={alpha} M={M} prefill={prefill}", fs.metrics_view(m),
+                        rm, s.cpu().numpy(), rs, f.cpu().numpy(), rf)
+    q = rng.integers(1, 12, size=(40, 6)).astype(np.int32)
+    for Bq in (2, 3):
+        check_opt(dev, f"optimum B={Bq} alpha={alpha}", np.zeros_like(q), np.zeros_like(q), q,
+                  B=Bq, alpha=alpha, M_kv=14)
+
+
+@pytest.mark.parametrize("B", [2, 65, 130])
+def test_fairness_budget_beyond_the_last_step(dev, B):
+    """Releases near the largest makespan (2^31 - 648): min_s + alpha + 1 lies beyond 2^31 for an
+    ordinary alpha too.  The schedule is that of the same jobs released at step 0, later."""
+    rng = np.random.default_rng(B)
+    n, late = 20, (1 << 31) - 648 - 20 * 120 - 10
+    o = rng.integers(1, 60, size=(6, n)).astype(np.int32)
+    z = np.zeros_like(o)
+    kw = dict(policy="isjl", B=B, alpha=4000, M_kv=70, cost_c=0, cost_tau=2)
+    for prefill in (False, True):
+        log(f"late releases B={B} prefill={prefill}")
+        ref, rs, rf = oracle.simulate(z, z, o, schedule=True,
+                                      flags=oracle.FLAG_PREFILL if prefill else 0, **kw)
+        got, gs, gf = gpu_sim(dev, z + np.int32(late), z, o, prefill=prefill, **kw)
+        assert np.array_equal(got["T"], ref["T"] + late)
+        assert np.array_equal(gs, rs + late) and np.array_equal(gf, rf + late)
+        for f in ("E", "C", "W", "sum_extent", "busy_steps", "peak_kv", "max_active"):
+            assert np.array_equal(got[f], ref[f]), f
