@@ -9,7 +9,8 @@ import pytest
 import oracle
 from oracle import ALPHA_INF
 from test_gpu_opt import check as check_opt
-from test_gpu_simulate import assert_same, dev, gpu_sim, log  # noqa: F401  (dev: the fixture)
+from test_gpu_simulate import (ISJL_VARIANTS, assert_same, check_copies, compute_units,  # noqa: F401
+                               dev, gpu_sim, log, plan_links_in_hbm)  # (dev: the fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -161,7 +162,7 @@ def test_fill_sweep_over_many_slots(dev, policy, alpha, n, B):
 def test_pack_scan_batches(dev, n, B, alpha):
     """Phase ONE's pack scan over batches of 64 candidates: packs that span batches, spare and
     long workers, candidates that fit nowhere (runs of them, to the next batch and to the end of
-    the queue), no candidate at all; plan links in LDS and in HBM."""
+    the queue), no candidate at all; plan links in LDS."""
     rng = np.random.default_rng(n + B + alpha)
     size = (8, n)
     z = np.zeros(size, np.int32)
@@ -212,24 +213,29 @@ def test_rescoring_halves(dev, n):
         assert np.array_equal(v.cpu().numpy().astype(np.uint32), rv)
 
 
-@pytest.mark.parametrize("prefill", [False, True])
+@pytest.mark.parametrize("variant", list(ISJL_VARIANTS))
 @pytest.mark.parametrize("B", [16, 100, 200, 500])
-def test_plan_links_in_hbm_for_large_batches(dev, B, prefill):
+@pytest.mark.parametrize("n,lds_waves,hbm_waves", [(2000, 12, 16), (2500, 6, 8)])
+def test_plan_links_in_hbm_for_large_batches(dev, n, lds_waves, hbm_waves, B, variant):
     """The plan-queue links move to HBM scratch only where the batch is larger than what the LDS
-    lets run at once (3,072 instances of 2,000 jobs): 3,200 copies of 8 instances, each copy
-    equal to the oracle's result."""
+    lets run at once with them (12 waves per CU at 2,000 jobs, 6 at 2,500, whose bitmap takes two
+    words per lane): copies of 8 instances, just above that (all resident at once without them,
+    taking the kernels that turn the issue priority) and beyond what is resident without them."""
     rng = np.random.default_rng(B)
-    a, p, o = (rng.integers(lo, hi, size=(8, 2000)).astype(np.int32)
+    a, p, o = (rng.integers(lo, hi, size=(8, n)).astype(np.int32)
                for lo, hi in ((0, 300), (0, 40), (1, 200)))
     a.sort(axis=1)
     a[7] = rng.permutation(a[7])
-    kw = dict(policy="isjl", B=B, alpha=45, M_kv=70 * B, cost_c=3, cost_tau=2)
-    log(f"plan links in HBM B={B} prefill={prefill}")
-    got, gs, gf = gpu_sim(dev, *(np.tile(x, (400, 1)) for x in (a, p, o)), prefill=prefill, **kw)
-    ref, rs, rf = oracle.simulate(a, p, o, schedule=True,
-                                  flags=oracle.FLAG_PREFILL if prefill else 0, **kw)
-    assert_same(f"B={B}", got, np.tile(ref, 400), gs, np.tile(rs, (400, 1)), gf,
-                np.tile(rf, (400, 1)))
+    u = o + rng.integers(0, 60, size=o.shape).astype(np.int32)
+    kw = dict(B=B, alpha=45, M_kv=70 * B, cost_c=3, cost_tau=2)
+    units = compute_units(dev)
+    opt, _ = ISJL_VARIANTS[variant]
+    assert not plan_links_in_hbm(lds_waves * units, n, **opt, **kw)
+    for waves in (lds_waves, hbm_waves):
+        copies = waves * units // 8 + 1
+        assert plan_links_in_hbm(8 * copies, n, **opt, **kw)
+        check_copies(dev, f"links in HBM n={n} B={B} {variant} {8 * copies} instances", a, p, o,
+                     u, copies, variant, **kw)
 
 
 def test_host_arrays_of_every_size_and_thread(dev):

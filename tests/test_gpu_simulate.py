@@ -48,6 +48,63 @@ def gpu_sim(dev, a, p, o, schedule=True, **kw):
     return m, None, None
 
 
+def compute_units(dev):
+    import torch
+    return torch.cuda.get_device_properties(dev).multi_processor_count
+
+
+def plan_links_in_hbm(n_inst, n, prefill=False, resume_fill=False, **kw):
+    """Whether an ISJL call of this shape keeps its plan-queue links in device
+    scratch, from the scratch that the library computes for it: the rank table (2
+    bytes per job, rows rounded up to 64) alone, or with 4 bytes per job (rows
+    rounded up to a power of two) beside it."""
+    import ctypes
+    need = fs.lib()["_ZN2fs21simulate_scratch_needEPK13fsched_paramsliPm"]
+    need.restype = ctypes.c_int
+    need.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p]
+    p = fs.make_params("isjl", device=True, prefill=prefill, resume_fill=resume_fill, **kw)
+    size = ctypes.c_size_t(0)
+    assert need(ctypes.byref(p), n_inst, n, ctypes.byref(size)) == 0
+
+    def table(row):
+        return -(-n_inst * row // 256) * 256
+
+    rank = table(-(-n // 64) * 64 * 2)
+    links = table(4 * max(64, 1 << (n - 1).bit_length()))
+    assert size.value in (rank, rank + links)
+    return size.value == rank + links
+
+
+# ISJL and its variants: options of the call, and whether the sizes are predicted
+ISJL_VARIANTS = {"plain": ({}, False), "prefill": (dict(prefill=True), False),
+                 "resume": (dict(resume_fill=True), False), "robust": ({}, True),
+                 "robust prefill": (dict(prefill=True), True)}
+
+
+def check_copies(dev, ctx, a, p, o, u, copies, variant, **kw):
+    """`copies` copies of the instances in one call of an ISJL variant, each copy
+    equal to the oracle's result."""
+    import torch
+    opt, predicted = ISJL_VARIANTS[variant]
+    log(ctx)
+    tabs = (a, p, o) + ((u,) if predicted else ())
+    ts = [torch.from_numpy(np.ascontiguousarray(x)).to(dev).repeat(copies, 1) for x in tabs]
+    flags = (oracle.FLAG_PREFILL if opt.get("prefill") else 0) | \
+        (oracle.FLAG_RESUME_FILL if opt.get("resume_fill") else 0)
+    if predicted:
+        got = fs.simulate_robust(*ts, schedule=True, **opt, **kw)
+        ref = oracle.simulate_robust(a, p, o, u, schedule=True, flags=flags, **kw)
+    else:
+        got = fs.simulate(*ts, policy="isjl", schedule=True, **opt, **kw)
+        ref = oracle.simulate(a, p, o, policy="isjl", schedule=True, flags=flags, **kw)
+    torch.cuda.synchronize()
+    m, s, f = (x.reshape(copies, len(a), -1) for x in got)
+    assert_same(ctx, fs.metrics_view(m[0]), ref[0], s[0].cpu().numpy(), ref[1],
+                f[0].cpu().numpy(), ref[2])
+    for x in (m, s, f):  # the other copies equal the first
+        assert bool((x == x[:1]).all()), ctx
+
+
 def first_divergence(gs, rs):
     """Instance and job of the earliest start at which two schedules differ."""
     rows = np.nonzero((gs != rs).any(1))[0]
@@ -439,42 +496,36 @@ def test_rank_scratch_reuse_across_calls_and_streams(dev):
 @pytest.mark.parametrize("alpha", [2, 40, 300])
 def test_plan_links_in_hbm(dev, alpha):
     """ISJL with up to 8 slots per lane and 2,000 jobs: the plan-queue links would
-    cap a CU below 16 waves in LDS, so they go to HBM scratch (also for the
-    predicted-size and prefill variants); 4 and 8 slots per lane also take the
-    kernels held to 128 VGPRs."""
+    cap a CU at 12 waves in LDS, so they go to HBM scratch in a batch larger than
+    what then runs at once (also for the predicted-size and prefill variants) and
+    stay in LDS in a smaller one; 4 and 8 slots per lane also take the kernels held
+    to 128 VGPRs."""
+    many = 12 * compute_units(dev) // 5 + 1  # copies of 5 instances
     rng = np.random.default_rng(zlib.crc32(f"qlinks:{alpha}".encode()))
     for B, M, arr in ((100, 0, 0), (128, 12000, 4000), (70, 6000, -3000), (200, 30000, 3000),
                       (512, 0, 0), (400, 45000, -3000)):
         a, p, o = workload.random_tables(rng, 5, 2000, 60, 200, max_arrival=abs(arr),
                                          sorted_arrivals=arr > 0)
         kw = dict(B=B, alpha=alpha, M_kv=M, cost_c=3, cost_tau=1)
-        ctx = f"plan links in HBM alpha={alpha} B={B} M={M} arrivals={arr}"
-        log(ctx)
-        check(dev, ctx, a, p, o, policy="isjl", **kw)
-        log(ctx + " prefill")
-        got, gs, gf = gpu_sim(dev, a, p, o, policy="isjl", prefill=True, **kw)
-        ref, rs, rf = oracle.simulate(a, p, o, policy="isjl", schedule=True,
-                                      flags=oracle.FLAG_PREFILL, **kw)
-        assert_same(ctx + " prefill", got, ref, gs, rs, gf, rf)
-        log(ctx + " robust")
         u = workload.prediction_upper(o, 0.5, seed=B)
-        import torch
-        ts = [torch.from_numpy(np.ascontiguousarray(x)).to(dev) for x in (a, p, o, u)]
-        raw, st, fi = fs.simulate_robust(*ts, schedule=True, **kw)
-        torch.cuda.synchronize()
-        ref, rs, rf = oracle.simulate_robust(a, p, o, u, schedule=True, **kw)
-        assert_same(ctx + " robust", fs.metrics_view(raw), ref, st.cpu().numpy(), rs,
-                    fi.cpu().numpy(), rf)
+        for copies, hbm in ((1, False), (many, True)):
+            for variant, (opt, _) in ISJL_VARIANTS.items():
+                assert plan_links_in_hbm(5 * copies, 2000, **opt, **kw) == hbm
+                ctx = f"links in HBM: {hbm} alpha={alpha} B={B} M={M} arrivals={arr} {variant}"
+                check_copies(dev, ctx, a, p, o, u, copies, variant, **kw)
 
 
 @pytest.mark.parametrize("policy,alpha", [("fcfs", ALPHA_INF), ("sjf", ALPHA_INF), ("ljf", 4),
                                           ("isjl", 40), ("isjl", ALPHA_INF)])
 def test_one_round_and_many_round_launches(dev, policy, alpha):
-    """A grid whose waves are all resident at once takes the kernels that turn
-    each wave's issue priority with its event count; a larger grid the kernels
-    without.  On the same instances both give the same metrics and schedules
-    (1, 2, 4 and 8 slots per lane; sorted, unsorted and no releases), and the
-    first instances match the oracle."""
+    """A grid whose waves are all resident at once, with more of them than SIMDs
+    (four per CU), takes the kernels that turn each wave's issue priority with its
+    event count; a larger or smaller grid the kernels without.  On the same
+    instances all give the same metrics and schedules (1, 2, 4 and 8 slots per
+    lane; sorted, unsorted and no releases), and the first instances match the
+    oracle."""
+    turning = 5 * compute_units(dev)
+    assert 256 < turning < 12288
     rng = np.random.default_rng(zlib.crc32(f"rounds:{policy}:{alpha}".encode()))
     for B, arr in ((50, 400), (128, -300), (200, 300), (300, 0)):
         a, p, o = workload.random_tables(rng, 12288, 300, 40, 120, max_arrival=abs(arr),

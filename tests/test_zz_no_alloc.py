@@ -10,6 +10,7 @@ import pytest
 
 import workload
 import paper_2608_02244_amd as fs
+from test_gpu_simulate import compute_units, plan_links_in_hbm
 
 pytestmark = pytest.mark.gpu
 
@@ -48,10 +49,17 @@ def both(dev, name, n_inst, **kw):
 
 
 def test_noalloc_equals_simulate_two_calls(dev):
-    # first call: ISJL at a finite alpha with 128 workers uses both parts of the
-    # scratch (rank table and plan-queue links); second: fewer, shorter instances
-    log("noalloc call 1: bimodal_sweep 512 instances, ISJL alpha=256")
-    both(dev, "bimodal_sweep_4096x2000", 512, policy="isjl", alpha=256)
+    # first calls: ISJL at a finite alpha with more instances than run at once
+    # with the plan-queue links in LDS (12 waves per CU) use both parts of the
+    # scratch (rank table and links), with 128 and 512 workers; then fewer and
+    # shorter instances, which use the rank table alone
+    many = 12 * compute_units(dev) + 40
+    for name, alpha in (("bimodal_sweep_4096x2000", 256), ("pareto_65536x2000", 128)):
+        w = workload.WORKLOADS[name]
+        assert plan_links_in_hbm(many, w.n_jobs, B=w.B, alpha=alpha, M_kv=w.M_kv)
+        assert not plan_links_in_hbm(192, w.n_jobs, B=w.B, alpha=alpha, M_kv=w.M_kv)
+        log(f"noalloc call 1: {name} {many} instances, ISJL alpha={alpha}")
+        both(dev, name, many, policy="isjl", alpha=alpha)
     log("noalloc call 2: pareto 192 instances, ISJL alpha=128 (8 slots per lane)")
     both(dev, "pareto_65536x2000", 192, policy="isjl", alpha=128)
     log("noalloc call 3: lognormal 96 instances, ISJL alpha=64")
