@@ -534,22 +534,29 @@ def test_one_round_and_many_round_launches(dev, policy, alpha):
         ctx = f"one round vs many policy={policy} alpha={alpha} B={B} arrivals={arr}"
         log(ctx)
         big, bs, bf = gpu_sim(dev, a, p, o, **kw)
-        small, ss, sf = gpu_sim(dev, a[:256], p[:256], o[:256], **kw)
-        assert_same(ctx, small, big[:256], ss, bs[:256], sf, bf[:256])
+        for k in (turning, 256):
+            small, ss, sf = gpu_sim(dev, a[:k], p[:k], o[:k], **kw)
+            assert_same(f"{ctx}, {k} instances", small, big[:k], ss, bs[:k], sf, bf[:k])
         ref, rs, rf = oracle.simulate(a[:6], p[:6], o[:6], schedule=True, **kw)
         assert_same(ctx + " oracle", small[:6], ref, ss[:6], rs, sf[:6], rf)
 
 
-@pytest.mark.parametrize("variant", ["prefill", "robust", "robust_prefill"])
+@pytest.mark.parametrize("variant", ["prefill", "robust", "robust_prefill", "fcfs_prefill",
+                                     "ljf_prefill", "sjf_prefill"])
 def test_one_round_and_many_round_launches_variants(dev, variant):
-    """The prefill and predicted-size variants of ISJL (alpha = 40) take the
-    turning-priority kernels in a grid resident at once too: the same
-    instances in a one-round and a many-round launch give the same metrics and
-    schedules, and the first instances match the oracle."""
+    """The prefill variants of every policy and the predicted-size ones of ISJL
+    (alpha = 40) take the turning-priority kernels in a grid resident at once with
+    more waves than SIMDs too: the same instances in such a launch, a many-round
+    one and one with at most a wave per SIMD give the same metrics and schedules,
+    and the first instances match the oracle."""
     import torch
+    turning = 5 * compute_units(dev)
+    assert 256 < turning < 12288
     rng = np.random.default_rng(zlib.crc32(f"rounds:{variant}".encode()))
     pre = variant.endswith("prefill")
     rob = variant.startswith("robust")
+    policy = variant[:-len("_prefill")] if variant in ("fcfs_prefill", "ljf_prefill",
+                                                       "sjf_prefill") else "isjl"
     for B, arr in ((50, 400), (128, -300), (300, 0)):
         a, p, o = workload.random_tables(rng, 12288, 300, 40, 120, max_arrival=abs(arr),
                                          sorted_arrivals=arr > 0)
@@ -564,19 +571,20 @@ def test_one_round_and_many_round_launches_variants(dev, variant):
             if rob:
                 raw, st, fi = fs.simulate_robust(*ts, prefill=pre, schedule=True, **kw)
             else:
-                raw, st, fi = fs.simulate(*ts, policy="isjl", prefill=pre, schedule=True, **kw)
+                raw, st, fi = fs.simulate(*ts, policy=policy, prefill=pre, schedule=True, **kw)
             torch.cuda.synchronize()
             return fs.metrics_view(raw), st.cpu().numpy(), fi.cpu().numpy()
 
         big, bs, bf = run(12288)
-        small, ss, sf = run(256)
-        assert_same(ctx, small, big[:256], ss, bs[:256], sf, bf[:256])
+        for k in (turning, 256):
+            small, ss, sf = run(k)
+            assert_same(f"{ctx}, {k} instances", small, big[:k], ss, bs[:k], sf, bf[:k])
         flags = oracle.FLAG_PREFILL if pre else 0
         if rob:
             ref, rs, rf = oracle.simulate_robust(a[:4], p[:4], o[:4], u[:4], schedule=True,
                                                  flags=flags, **kw)
         else:
-            ref, rs, rf = oracle.simulate(a[:4], p[:4], o[:4], policy="isjl", schedule=True,
+            ref, rs, rf = oracle.simulate(a[:4], p[:4], o[:4], policy=policy, schedule=True,
                                           flags=flags, **kw)
         assert_same(ctx + " oracle", small[:4], ref, ss[:4], rs, sf[:4], rf)
 
