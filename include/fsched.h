@@ -38,11 +38,17 @@
  *     call (host mode) or after the stream passes the call (device mode).
  *   - fsched_simulate, fsched_simulate_robust and fsched_bruteforce_opt (every
  *     policy but FCFS) also take a scratch table of 2 bytes per job (rows
- *     rounded up to 64 jobs) on `stream`, from a memory pool the library creates
- *     once per device and keeps for the process: freed on the stream after the
- *     call's kernels, it stays in the pool for the next call (else the
- *     device's default pool is used).  If neither can supply it the call
- *     returns FSCHED_ENOMEM before enqueuing any kernel.
+ *     rounded up to 64 jobs) on `stream`, and ISJL at a finite alpha with
+ *     min(B, n_jobs) <= 512 may take its plan-queue links there too (4 bytes
+ *     per job, rows rounded up to a power of two, at least 64): it does when in
+ *     LDS they would let fewer than 16 waves share a compute unit (from 1,025
+ *     jobs up) and the batch has more instances than the device then runs at
+ *     once (that number of waves per unit times the units; 3,072 instances at
+ *     1,025 to 2,048 jobs and 1,536 beyond on 256 units).  Both come from a
+ *     memory pool the library creates once per device and keeps for the process:
+ *     freed on the stream after the call's kernels, they stay in the pool for the
+ *     next call (else the device's default pool is used).  If neither can supply
+ *     them the call returns FSCHED_ENOMEM before enqueuing any kernel.
  *   - Return codes are FSCHED_OK or a negative FSCHED_E* code; outputs are
  *     undefined on error.  Argument errors (null pointers, bad sizes or
  *     parameters) are detected before any work is enqueued.  In device mode the
@@ -232,8 +238,9 @@ int fsched_cost_decompose(const fsched_params* p, int64_t n_inst, int32_t n_jobs
  * A first pass of the search keeps the
  * search's memo in LDS and stops a search after 2^22 steps; the searches it
  * stops are run again by a second pass with a memo of 2^20 entries per wave in
- * device scratch (256 MiB from the library's pool, with the instance list;
- * stream-ordered, released after the call) and a cap of 2^28 steps.  Only a
+ * device scratch (256 MiB from the library's pool, with three lists of
+ * instances, 12 bytes per instance in all; stream-ordered, released after the
+ * call) and a cap of 2^28 steps.  Only a
  * search past that cap gets T_opt = FSCHED_T_INTERNAL (host mode: EINTERNAL);
  * on the tiny workload (4,096 instances, B = 3 and 4, alpha up to 19, with and
  * without a KV budget) none does.  If the scratch cannot be had, the second
@@ -252,20 +259,19 @@ int fsched_bruteforce_opt(const fsched_params* p, int64_t n_inst, int32_t n_jobs
  * device memory during the call: code being captured into a HIP graph, tight
  * serving loops, harnesses that forbid hipMalloc.  It allocates nothing: no
  * hipMalloc / hipFree / pool allocation and no host staging.  Its scratch (the
- * rank table of 2 bytes per job, rows rounded up to 64 jobs, for every policy
- * but FCFS; for ISJL with at most 512 workers and a finite alpha, when the
- * plan-queue links do not fit LDS, 4 bytes per job rounded up to a power of two
- * (at least 64)) is a fixed buffer of FSCHED_NOALLOC_SCRATCH_BYTES per device,
- * part of the library's image and held by each device the library runs on
- * until the process ends; its device address is looked up once per device, on
- * that device's first call.
+ * rank table and, under the same rule, the plan-queue links of the conventions
+ * above: whether a shape needs the links depends on the number of instances and
+ * on the device's compute units) is a fixed buffer of
+ * FSCHED_NOALLOC_SCRATCH_BYTES per device, part of the library's image and held
+ * by each device the library runs on until the process ends; its device address
+ * is looked up once per device, on that device's first call.
  *   - p->flags must include FSCHED_F_DEVICE_PTRS (EINVAL otherwise); every
  *     array is a device pointer on the current device, and outputs as in
  *     fsched_simulate.  FSCHED_F_SYNC synchronises the stream before return.
  *   - A call whose scratch would exceed FSCHED_NOALLOC_SCRATCH_BYTES returns
  *     FSCHED_ESCRATCH before enqueuing anything (e.g. at 2,000 jobs per
- *     instance, B = 512 and a finite alpha, 12 KiB per instance: 5,461
- *     instances fit 64 MiB).
+ *     instance, B = 512 and a finite alpha, 12 KiB per instance with the links:
+ *     5,461 instances fit 64 MiB).
  *   - Every call on one device shares that device's buffer: calls that overlap
  *     in time on one device (on different streams, or from several threads)
  *     race and give undefined results.  Calls in order on one stream are safe.
@@ -288,8 +294,9 @@ int fsched_abi_version(void);
 int fsched_last_hip_error(void);
 
 /* Returns to the current device the memory that the library's scratch pool on
- * it keeps between calls (the rank tables, see the conventions above); later
- * calls take it from the device again.  Memory of calls still in flight on a
+ * it keeps between calls (the rank tables, plan-queue links and staged host
+ * arrays of at most 4 MiB a call of the conventions above, and the second pass's
+ * scratch of the exact optimum); later calls take it from the device again.  Memory of calls still in flight on a
  * stream is not released.  FSCHED_OK (also when the pool was never created),
  * or FSCHED_EDEVICE. */
 int fsched_release_cache(void);
