@@ -27,7 +27,8 @@ struct SimArgs {
   int32_t NP;         // n rounded up to a power of two (>= 64)
   int32_t wave_words; // LDS words per wave
   int32_t off_q;      // word offset of the plan-queue links (ISJL)
-  int32_t off_stage;  // word offset of the gather / release buffer (not FCFS)
+  int32_t off_stage;  // word offset of the gather / release buffer (FCFS: of the 64 words that
+                      // its sweeps pack into, with 2 or more slots per lane or PREFILL)
   int32_t resume;     // ISJL: Phase TWO resumes once A_max <= alpha (1) or waits
                       // for an empty machine (0)
   int32_t share_simds;  // several of the launch's waves run on one SIMD

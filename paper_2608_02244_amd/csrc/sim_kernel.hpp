@@ -27,7 +27,10 @@
 //   LDS   W[r]     jobs in the policy's priority order, packed (len << 12 | id)
 //         QN[r]    next job in the same ISJL plan queue (uint16, ISJL)
 //         STG[j]   gather buffer of the first queued ranks (uint16, not FCFS)
-//         PEND[i]  released ranks on their way into the bitmap (aliases STG)
+//         PEND[i]  released ranks on their way into the bitmap, and up to 64
+//                  slots or completions that a sweep packs (aliases STG; FCFS
+//                  has it, 64 words, with 2 or more slots per lane or the prompt
+//                  prefilled, and its other kernels never touch it)
 //   The drain sweep sorts the active slots in registers; up to 64 of them are
 //   first packed into one register through the gather buffer.
 //   VGPR  K worker slots per lane: worker w lives in slot w/64 of lane w%64
@@ -140,7 +143,8 @@ struct PoolBits {
 // differences of that kind are read from it.
 struct SimState {
   int t, ndone, nact, min_s, max_s, min_end;
-  int res;              // KV reservations of the active jobs
+  int res;              // KV reservations of the active jobs (only with a KV budget: a
+                        // plan run without one leaves them out, and no one reads them)
   uint32_t sum_s;       // summed start of the active jobs, modulo 2^32
   uint64_t sum_start;   // summed start of every admitted job
   // prefill variant: largest prompt - start and summed prompt of the active jobs
@@ -190,7 +194,9 @@ struct SpanSums {
 // PRE: the prompt is prefilled at admission (Section 1 with eq. (1)'s decode
 // progress): a job runs one step per output token, reserves prompt + output and
 // its footprint in the batch cost is prompt + progress; fairness stays on
-// progress.  The sweeps are off (completions are taken one event at a time).
+// progress.  The drain, A_max and fill sweeps are off; a release sweep of its own
+// (up to 8 slots per lane) folds up to 64 completions in, ISJL with up to 2 slots
+// per lane takes plan runs, and every other completion is an event.
 // FILL: with the fill sweep (below).
 // QH: ISJL with up to 8 slots per lane whose plan-queue links are in HBM
 // scratch (else in LDS).  Every kernel with up to 8 slots per lane but FCFS's
