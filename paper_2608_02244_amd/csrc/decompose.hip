@@ -447,8 +447,8 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
     const int fsl = smask ? __builtin_ctzll(smask) : WAVE;  // first start of the chunk
     const uint64_t pre = fsl >= WAVE ? ~0ull : ((1ull << fsl) - 1);
     const bool open_in = g_nst > 0;  // then the chunk begins with starts of that group
-    const bool max_kept =
-        open_in ? gmask != 0 : (nmax > 0 && __builtin_popcountll(emax & pre) < nmax);
+    const bool max_kept = open_in || (nmax > 0 && __builtin_popcountll(emax & pre) < nmax);
+    const int g_end = 63 - __builtin_clzll(gmask);  // the chunk's last group end
     const bool fast = min_s != IDLE32 && nmin > 0 && max_kept && !(gmask & ballot(cnt_p == 0)) &&
                       __builtin_popcountll(emin) < nmin && !(emask & ballot(sj == lat));
     if (fast) {
@@ -470,13 +470,13 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
         nmax -= __builtin_popcountll(emax);
       }
       // starts after the chunk's last group end open the next group
-      const uint64_t st = smask & bits_above(gmask ? 63 - __builtin_clzll(gmask) : -1);
+      const uint64_t st = smask & bits_above(g_end);
       g_nst = __builtin_popcountll(st);
       if (st) {
         gfirst = base + __builtin_ctzll(st);
         glast = base + 63 - __builtin_clzll(st);
       }
-      if (gmask) cnt_last = readlane(cnt_p, 63 - __builtin_clzll(gmask));
+      cnt_last = readlane(cnt_p, g_end);
     } else {
       const int min0 = min_s, max0 = max_s;  // in force before the chunk's first visit
       uint64_t chg = 0;                      // visited group ends
@@ -612,7 +612,7 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
         nmax -= __builtin_popcountll(emax & after);
         const uint64_t glast_m = gmask & after;
         if (glast_m) open = false;
-        const uint64_t tail = bits_above(gmask ? 63 - __builtin_clzll(gmask) : -1) & after;
+        const uint64_t tail = bits_above(g_end) & after;
         const uint64_t st = smask & tail;
         if (st) {
           if (!open) {
@@ -624,7 +624,7 @@ __attribute__((amdgpu_waves_per_eu(NP2 <= 4096 ? 4 : 2))) void decompose_kernel(
           open = true;
         }
         if (!open) g_nst = 0;
-        if (gmask) cnt_last = readlane(cnt_p, 63 - __builtin_clzll(gmask));
+        cnt_last = readlane(cnt_p, g_end);
       }
       // earliest / latest start in force at each group end of the chunk
       {
