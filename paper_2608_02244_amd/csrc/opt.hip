@@ -920,7 +920,10 @@ hipError_t launch_opt(const OptArgs& a0, hipStream_t s) {
       // instances at alpha = 2 took 1.82 ms with it, 1.87 / 1.98 / 3.07 ms with
       // limits of 5,120 / 4,096 / 2,560 entries, which leave more to the second
       // launch); a second one those within PAIR_ENTRIES_MAX, when a table can be
-      // larger at all.
+      // larger at all, by 1,024 blocks that claim from the list: two of them share
+      // a CU's LDS at the largest table, seven at alpha = 4's (256 blocks took 3.8
+      // ms there, 1,024 2.7, 4,096 2.5; at alpha = 7 and 11 10.4 and 13.2 ms, then
+      // 4.6 and 6.0 with either).
       const int64_t per_job = (int64_t)std::min(a.alpha, OPT_LEN_LIMIT - 1) + 1;
       const int64_t worst = ((int64_t)1 << a.n) * (1 + a.n * per_job);
       const int first = (int)std::min<int64_t>(worst, PAIR_ENTRIES);

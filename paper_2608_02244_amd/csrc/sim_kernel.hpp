@@ -201,19 +201,25 @@ struct SpanSums {
 // QH: ISJL with up to 8 slots per lane whose plan-queue links are in HBM
 // scratch (else in LDS).  Every kernel with up to 8 slots per lane but FCFS's
 // is held to 128 VGPRs, so that 4 waves share a SIMD where the LDS allows 16
-// per CU (FCFS's 4- and 8-slot kernels ran slower that way and keep 3).
+// per CU.  FCFS's 4- and 8-slot kernels keep 3: with an event per completion
+// they ran 13.4 ms at 3 and 14.6 at 4 (16,384 x 2,000 at B = 512).  With the fill
+// sweep little is left between the two: 1.320 ms at 3, 1.304 at 4 (B = 256 1.198
+// and 1.188; 4,096 x 2,000 at B = 200 538 and 535 us).
 template <int POL, int K, int NW, bool ROB, bool PRE, bool FILL, bool QH = false,
           bool FAIR = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (K <= 8 && POL != POL_FCFS) ? 4 : (K <= 8 ? 3 : 1)))) void simulate_kernel(SimArgs a) {
   static_assert(!ROB || POL == POL_ISJL, "predicted sizes: ISJL only");
   static_assert(!FILL || (!ROB && !PRE && POL != POL_LJF), "fill sweep variants");
   extern __shared__ uint32_t lds_raw[];
-  // With 4 or 8 slots per lane (but FCFS) the wave's index in its block is
-  // taken into a scalar register: every row pointer derived from the instance
-  // is then scalar, which is what brings those kernels under 128 VGPRs.  With one
-  // slot per lane it shortens the event loop's address chains (256 x 2,000 ISJL
-  // at B = 16: 918 -> 901 us); the kernels with two ran slower with it (445 ->
-  // 451 us at B = 128), their scalar registers being the scarcer ones.
+  // With 4 or 8 slots per lane (but FCFS: 1.320 -> 1.345 ms at B = 512, 538 -> 558
+  // us at B = 200) the wave's index in its block is taken into a scalar register:
+  // every row pointer derived from the instance is then scalar, which is what
+  // brings those kernels under 128 VGPRs.  With one slot per lane it shortens the
+  // event loop's address chains (256 x 2,000 ISJL at B = 16: 918 -> 901 us).  With
+  // two, ISJL's plan runs at a large finite alpha are slower with it, their scalar
+  // registers being the scarcer ones (4,096 x 2,000 at B = 128: alpha = 256 399 ->
+  // 404 us, 1024 1.11 -> 1.16 ms), the others 3 to 6 % faster (alpha = 16 216 ->
+  // 209, infinite 368 -> 359, prompt prefilled 2,888 -> 2,728, LJF 149 -> 139).
   constexpr bool WIB_S = K <= 8 && K != 2 && POL != POL_FCFS;
   const int wib = WIB_S ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
                         : (int)(threadIdx.x >> 6);
@@ -1416,7 +1422,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
     // are of this kind (4,096 x 2,000 at B = 128, alpha = 256: 593 -> 446 us; one
     // instance of 200 jobs at B = 50: 148 -> 111 us).  Up to 2 slots per lane: the
     // wide kernels ran no faster (3.13 ms at B = 512) or slower (4.51 -> 4.86 ms
-    // with the prompt prefilled, 0.93 -> 0.99 ms with predicted sizes).
+    // with the prompt prefilled, 0.93 -> 0.99 ms with predicted sizes).  Not tried
+    // with fewer than 4 jobs planned, where the run's set-up is not earned back
+    // (from 1 on: 399 -> 406 us at alpha = 256, lognormal 4,096 x 1,000 at alpha =
+    // 256 315 -> 319, though alpha = 64 232 -> 227; from 8 on 402, from 16 on 429,
+    // and the one instance 54 -> 69 us on device arrays).
     if constexpr (PLAN_RUN) {
       const int spare = Beff - S.nact - (w0_timer ? 1 : 0);  // idle, but worker 1 on its timer
       const bool p2 = mode == 0 && spare > 0;
@@ -1884,7 +1894,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K <= 2 || (
         };
         int N0 = ends_before(X);  // completions sorted
         if constexpr (K > 1) {
-          if (N0 > WAVE) {  // an earlier X with at most 64 of them
+          if (N0 > WAVE) {
+            // an earlier X with at most 64 of them, by halving until 48 or more
+            // are left (a halving costs K ballots, a short run a whole sweep).
+            // Stopping at 24 or 32 took 1.49 and 1.57 ms for 16,384 x 2,000 FCFS
+            // at B = 512, 48 1.32, 60 within 20 halvings 1.28; at B = 128 and 200,
+            // where runs end early, 60 was slower (422 -> 429, 538 -> 547 us).
             int hi = X;
             X = S.min_end;
             N0 = 0;
