@@ -1,6 +1,6 @@
 """The named workloads are the recorded bytes: the SHA-256 of each one's job
 tables (arrival, prompt, output in that order) equals the value stored in
-tests/golden/workload_sha256.json and quoted in the benchmark spec."""
+tests/golden/workload_sha256.json."""
 import hashlib
 import json
 import os
